@@ -17,6 +17,9 @@ For |y| <= 1 (the range of S = u_e sqrt(beta) below local Mach ~1.2) the
 FP32 path uses a shorter form: erf(y) = y P(y^2) with P the near-minimax
 polynomial of erf(sqrt(u)) / sqrt(u) on u in [0, 1] from mpmath's Chebyshev
 fit, 6 coefficients (fit error 4.1e-8).
+For |y| <= 1.25 (local Mach below ~1.5) the FP64 flux kernel uses the same
+form, erf(y)/2 = y P(y^2) with 14 coefficients on u in [0, 1.25^2] (fit error
+1.1e-18).
 Exponential (FP64): exp(r) on |r| <= ln2/2 by the degree-11 polynomial of
 mpmath's Chebyshev fit (fit error 3.2e-18; with the two-part reduction
 x = k ln2 + r, 1.4e-16 relative in double), and ln2 split into a double and
@@ -70,6 +73,14 @@ def small(n):
     return mp.chebyfit(f, [0, 1], n)  # highest power first
 
 
+def small64(edge, n):
+    def f(u):
+        if u == 0:
+            return 1 / mp.sqrt(mp.pi)
+        return mp.erf(mp.sqrt(u)) / (2 * mp.sqrt(u))
+    return mp.chebyfit(f, [0, mp.mpf(edge) ** 2], n)  # highest power first
+
+
 def exp_poly(deg):
     half = mp.log(2) / 2
     return mp.chebyfit(mp.exp, [-half, half], deg + 1)[::-1]  # lowest power first
@@ -103,6 +114,14 @@ def main():
     print("constexpr float kErfP32[kErfP32N] = {")
     for v in p32:
         print(f"    {mp.nstr(v, 12, min_fixed=0, max_fixed=0)}f,")
+    print("};")
+    p64 = small64("1.25", 14)
+    print("// erf(y) / 2 = y P(y^2) for |y| <= kErfNear64, P highest power first")
+    print("constexpr double kErfNear64 = 1.25;")
+    print(f"constexpr int kErfN64 = {len(p64)};")
+    print("constexpr double kErfPoly64[kErfN64] = {")
+    for v in p64:
+        print(f"    {mp.nstr(v, 20, min_fixed=0, max_fixed=0)},")
     print("};")
     print("// exp(r) = sum_k e_k r^k for |r| <= ln2/2 (lowest power first); ln2 = hi + lo")
     print(f"constexpr double kLog2e = {mp.nstr(1 / ln2, 20, min_fixed=0, max_fixed=0)};")

@@ -9,10 +9,12 @@
 // Negative arguments use erfc(y) = 2 - erfc(-y).  The reciprocal
 // inv = 1/(c + |y|) is an argument: the device kernels form it with a
 // refined hardware reciprocal, host callers by division.
-// In FP32, small arguments (|y| <= 1) use erf's odd polynomial instead (in
-// FP64 its extra constants cost the flux kernel a wave of occupancy).
+// In FP32, small arguments (|y| <= 1) use erf's odd polynomial instead.
 // The exponential is evaluated here too (exp_poly): a two-part reduction by
 // ln2 and a polynomial, without the library's range branches.
+// The FP64 flux body takes erf's odd polynomial where |S| <= 1.25
+// (half_erfc_near: 14 fma instead of a reciprocal and 22) and comes to the
+// form above only past it.
 // Evaluated with explicit fma and no implicit contraction, so equal
 // arguments give equal results wherever the function is inlined.
 #pragma once
@@ -45,11 +47,24 @@ __host__ __device__ inline float erfc_scaled_f(float a, float inv) {
     return t * r;
 }
 
+// q 2^k for an integral k, 0 or inf where |k| is past the exponent range.
+// On the device the conversion to an integer saturates by itself (two
+// instructions fewer than clamping k first); NaN converts to 0.
+__host__ __device__ inline double scale_pow2(double q, double k) {
+#ifdef __HIP_DEVICE_COMPILE__
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(k));
+    return ldexp(q, i);
+#else
+    return ldexp(q, (int)fmin(fmax(k, -2100.0), 2100.0));
+#endif
+}
+
 // exp(x): x = k ln2 + r with ln2 = hi + lo (Cody and Waite's two-part
 // constant, so that r is exact to well below an ulp), |r| <= ln2/2, exp(r)
 // by a degree-11 polynomial, times 2^k; 1.4e-16 relative.  No range
 // branches: for x below -746 or above 710 the scaling alone gives 0 or inf
-// (the exponent is clamped before its conversion to an integer), and the
+// (the exponent saturates in its conversion to an integer), and the
 // reduction stays accurate for |x| < 1e15, far past that; NaN propagates.
 __host__ __device__ inline double exp_poly(double x) {
 #pragma clang fp contract(off)
@@ -59,7 +74,7 @@ __host__ __device__ inline double exp_poly(double x) {
     double q = kExpPoly64[kExpN64 - 1];
 #pragma unroll
     for (int j = kExpN64 - 2; j >= 0; --j) q = fma(q, r, kExpPoly64[j]);
-    return ldexp(q, (int)fmin(fmax(k, -2100.0), 2100.0));
+    return scale_pow2(q, k);
 }
 
 // exp(-y^2) with the square split exactly into hi + lo (hi = fl(y*y)), so
@@ -68,7 +83,8 @@ __host__ __device__ inline double gauss(double y) {
 #pragma clang fp contract(off)
     const double hi = y * y;
     const double lo = fma(y, y, -hi);
-    return exp_poly(-hi) * (1.0 - lo);
+    const double e = exp_poly(-hi);
+    return fma(-lo, e, e);
 }
 
 // erfc(y) / 2 given gauss = exp(-y^2) and inv = 1/(kErfcC64 + |y|)
@@ -76,6 +92,17 @@ __host__ __device__ inline double half_erfc(double y, double gauss, double inv) 
 #pragma clang fp contract(off)
     const double h = (0.5 * gauss) * erfc_scaled(fabs(y), inv);
     return (y >= 0.0) ? h : 1.0 - h;
+}
+
+// erfc(-y) / 2 = 1/2 + y P(y^2) for |y| <= kErfNear64, within 2^-52 (half an
+// ulp of the sum and an ulp each of y^2 and y P, |y P| < 1/2)
+__host__ __device__ inline double half_erfc_near(double y) {
+#pragma clang fp contract(off)
+    const double u = y * y;
+    double r = kErfPoly64[0];
+#pragma unroll
+    for (int k = 1; k < kErfN64; ++k) r = fma(r, u, kErfPoly64[k]);
+    return fma(y, r, 0.5);
 }
 
 // FP32: for |y| <= 1 (local Mach below ~1.2) (1 - y P(y^2)) / 2 with a short

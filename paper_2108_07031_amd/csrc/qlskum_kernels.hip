@@ -1092,27 +1092,29 @@ struct Prim {
     double rho, u1, u2, p, sqb, bk, h, k;
 };
 
-// 1/d from the hardware reciprocal estimate refined by two Newton steps
-// (each squares the relative error; the result is within an ulp or two of
-// the rounded quotient) for d normal and finite -- the flux body's divisors
+// 1/d from the hardware reciprocal estimate r0 (relative error e below
+// 2^-22) refined by one third-order step r0 (1 + e + e^2), three fma where
+// two Newton steps take four; the result is within an ulp or two of the
+// rounded quotient, for d normal and finite -- the flux body's divisors
 // (2 beta of a state that passes the positivity check, the limiter's
 // denominator, which is zero or at least eps^2) are.  A correctly rounded
 // division costs several times more issue slots in this VALU-bound kernel.
 __device__ __forceinline__ double fast_rcp(double d) {
 #pragma clang fp contract(off)
-    double r = __builtin_amdgcn_rcp(d);
-    r = fma(r, fma(-d, r, 1.0), r);
-    return fma(r, fma(-d, r, 1.0), r);
+    const double r = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 
-// 1/sqrt(d) from the hardware estimate refined by two Newton steps
-// r <- r + (r/2)(1 - d r^2), for d positive, normal and finite (beta of a
-// state that passes the positivity check).
+// 1/sqrt(d) from the hardware estimate r refined by one third-order step:
+// with e = 1 - d r^2, 1/sqrt(d) = r (1 + e/2 + 3 e^2/8 + ...) (five
+// operations, two Newton steps take eight), for d positive, normal and finite
+// (beta of a state that passes the positivity check).
 __device__ __forceinline__ double fast_rsqrt(double d) {
 #pragma clang fp contract(off)
-    double r = __builtin_amdgcn_rsq(d);
-    r = fma(0.5 * r, fma(-(d * r), r, 1.0), r);
-    return fma(0.5 * r, fma(-(d * r), r, 1.0), r);
+    const double r = __builtin_amdgcn_rsq(d);
+    const double e = fma(-(d * r), r, 1.0);
+    return fma(r, e * fma(0.375, e, 0.5), r);
 }
 
 // sqrt(d) for d positive, normal and finite: s = d r with r the hardware
@@ -1136,11 +1138,11 @@ template <int POW>
 __device__ __forceinline__ bool q_to_prim(const double qt[4], const FlowParams &fp, Prim &s) {
 #pragma clang fp contract(off)
     const double beta = -0.5 * qt[3];
-    const double inv2b = -fast_rcp(qt[3]);
+    const double isqb = fast_rsqrt(beta);
+    const double inv2b = (0.5 * isqb) * isqb;
     s.u1 = qt[1] * inv2b;
     s.u2 = qt[2] * inv2b;
     const double uu = fma(s.u1, s.u1, s.u2 * s.u2);
-    const double isqb = fast_rsqrt(beta);
     s.sqb = beta * isqb;
     if (POW > 0) {
         s.rho = exp_poly(fma(beta, uu, qt[0])) * ipow<POW>(isqb);
@@ -1152,9 +1154,54 @@ __device__ __forceinline__ bool q_to_prim(const double qt[4], const FlowParams &
     s.h = s.p + rhoe;
     s.k = fma(0.5, s.p, rhoe);
     s.bk = kHalfRsqrtPi * isqb;
-    return (qt[3] < 0.0) && isfinite(s.rho) && isfinite(s.p) && isfinite(s.u1) &&
-           isfinite(s.u2);
+    // a non-finite u1, u2 or rho makes p non-finite (uu enters rho's exponent
+    // with the positive factor beta, and p = rho / (2 beta))
+    return (qt[3] < 0.0) && isfinite(s.p);
 }
+
+// erfc(y)/2 past |y| = kErfNear64, given gauss = exp(-y^2).  Few waves of a
+// transonic flow hold such a state (local Mach above ~1.5), so the
+// coefficients are read from memory in a loop instead of held in registers.
+struct ErfcTable {
+    double c[kErfcN64];
+};
+constexpr ErfcTable erfc_table() {
+    ErfcTable t{};
+    for (int k = 0; k < kErfcN64; ++k) t.c[k] = kErfcPoly64[k];
+    return t;
+}
+__constant__ ErfcTable kErfcTable = erfc_table();
+
+__device__ __forceinline__ double half_erfc_far(double y, double gauss) {
+#pragma clang fp contract(off)
+    const double t = kErfcC64 * fast_rcp(kErfcC64 + fabs(y));
+    const double u = fma(2.0, t, -1.0);
+    double r = kErfcTable.c[kErfcN64 - 1];
+#pragma unroll 1
+    for (int k = kErfcN64 - 2; k >= 0; --k) r = fma(r, u, kErfcTable.c[k]);
+    const double h = (0.5 * gauss) * (t * r);
+    return (y >= 0.0) ? h : 1.0 - h;
+}
+
+// Normal component u_e, S = u_e sqrt(beta), E = exp(-S^2) and A = erfc(-sg S)/2
+// of one split flux.  near() is straight-line code, exact for |S| up to
+// kErfNear64, so that the chains of several fluxes interleave; far() then
+// replaces A where |S| lies past it.  Which of the two a state takes depends
+// on its own S alone.
+struct HalfRange {
+    double ue, S, E, A;
+
+    __device__ __forceinline__ void near(const Prim &s, double ex, double ey, double sg) {
+#pragma clang fp contract(off)
+        ue = fma(s.u1, ex, s.u2 * ey);
+        S = ue * s.sqb;
+        E = gauss(S);
+        A = half_erfc_near(sg * S);
+    }
+    __device__ __forceinline__ void far(double sg) {
+        if (fabs(S) > kErfNear64) A = half_erfc_far(-sg * S, E);
+    }
+};
 
 // Kinetic split flux along the unit direction e; sg = +1 for G+, -1 for G-.
 // Half-range moments of the Maxwellian: with S = u_e sqrt(beta),
@@ -1162,29 +1209,33 @@ __device__ __forceinline__ bool q_to_prim(const double qt[4], const FlowParams &
 // serves both, see qlskum_erfc.h),
 //   G = [rho(u_e A + sg B), rho u (u_e A + sg B) + p A e,
 //        (p + rho e) u_e A + sg (p/2 + rho e) B].
-__device__ __forceinline__ void split_flux(const Prim &s, double ex, double ey, double sg,
-                                           double G[4]) {
+__device__ __forceinline__ void split_flux(const Prim &s, const HalfRange &h, double ex, double ey,
+                                           double sg, double G[4]) {
 #pragma clang fp contract(off)
-    const double ue = fma(s.u1, ex, s.u2 * ey);
-    const double S = ue * s.sqb;
-    const double E = gauss(S);
-    const double A = half_erfc(-sg * S, E, fast_rcp(kErfcC64 + fabs(S)));
-    const double B = E * s.bk;
-    const double sB = sg * B;
-    const double mass = s.rho * fma(ue, A, sB);
-    const double pA = s.p * A;
+    const double sB = sg * (h.E * s.bk);
+    const double mass = s.rho * fma(h.ue, h.A, sB);
+    const double pA = s.p * h.A;
     G[0] = mass;
     G[1] = fma(s.u1, mass, pA * ex);
     G[2] = fma(s.u2, mass, pA * ey);
-    G[3] = fma(s.h * ue, A, s.k * sB);
+    G[3] = fma(s.h * h.ue, h.A, s.k * sB);
+}
+
+__device__ __forceinline__ void split_flux(const Prim &s, double ex, double ey, double sg,
+                                           double G[4]) {
+    HalfRange h;
+    h.near(s, ex, ey, sg);
+    h.far(sg);
+    split_flux(s, h, ex, ey, sg, G);
 }
 
 // Venkatakrishnan limiter value for the increment delta of one component:
 //   phi = (D^2 + eps^2 + 2 delta D) / (D^2 + 2 delta^2 + delta D + eps^2)
 // with D = qmax - q (delta > 0) or qmin - q, the point's stored offsets dmax
 // and dmin.  The denominator is (D + delta/2)^2 + 7/4 delta^2 + eps^2 >=
-// eps^2 > 0: callers keep eps^2 at least 1e-300, so that coincident points
+// eps^2 > 0: callers keep eps^2 at least kEps2Min, so that coincident points
 // (D = delta = eps = 0, the one 0/0 case) give phi = 1 without a test here.
+constexpr double kEps2Min = 1e-150;  // its square is still a normal number
 __device__ __forceinline__ double venkat(double delta, double dmax, double dmin, double eps2) {
 #pragma clang fp contract(off)
     const double D = (delta > 0.0) ? dmax : dmin;
@@ -1194,6 +1245,21 @@ __device__ __forceinline__ double venkat(double delta, double dmax, double dmin,
     return num * fast_rcp(den);
 }
 
+// Two limiter values with one reciprocal, 1/a = b/(ab): the reciprocal costs
+// as much as seven other operations here, the three products three.
+__device__ __forceinline__ void venkat2(double da, const double *ba, double db, const double *bb,
+                                        double eps2, double &pa, double &pb) {
+#pragma clang fp contract(off)
+    const double Da = (da > 0.0) ? ba[0] : ba[4], Db = (db > 0.0) ? bb[0] : bb[4];
+    const double a2 = fma(Da, Da, eps2), b2 = fma(Db, Db, eps2);
+    const double na = fma(2.0 * da, Da, a2), nb = fma(2.0 * db, Db, b2);
+    const double ga = fma(da, Da, fma(2.0 * da, da, a2));
+    const double gb = fma(db, Db, fma(2.0 * db, db, b2));
+    const double r = fast_rcp(ga * gb);
+    pa = na * (r * gb);
+    pb = nb * (r * ga);
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -1201,7 +1267,10 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // Contribution of one neighbour entry (split flags f, offset (dx, dy) from p
-// to i) to the residual of p: the modified states q~_i and q~_p of eq. (28)
+// to i) to the residual of p.  Bound by FP64 issue: 494 VALU instructions with
+// the limiter, seven of them quarter-rate (a reciprocal per limiter value and
+// the general erfc everywhere took 630 with seventeen); the 2.5M-point launch
+// 1595 -> 1352 us.  Forms the modified states q~_i and q~_p of eq. (28)
 // (limited when LIMITER), their split fluxes, and w_b (G(q~_i) - G(q~_p))
 // added for each split stencil b the entry belongs to (one s half and one n
 // half at most).  w holds p's eight least-squares factors (see k_setup).
@@ -1231,7 +1300,7 @@ __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, doub
         }
     } else if (LIMITER) {
         const double e = fp.venkat_k * fast_sqrt(fma(dx, dx, dy * dy));
-        const double eps2 = fmax((e * e) * e, 1e-300);
+        const double eps2 = fmax((e * e) * e, kEps2Min);
         // -1/2 folded into the offsets: scaling by a power of two commutes
         // with rounding, so delta has the same bits as -1/2 (d . g)
         const double hx = -0.5 * dx, hy = -0.5 * dy;
@@ -1239,8 +1308,10 @@ __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, doub
         for (int r = 0; r < 4; ++r) {
             const double di = fma(hx, gi[r], hy * gi[4 + r]);
             const double d0 = fma(hx, gp[r], hy * gp[4 + r]);
-            qti[r] = fma(venkat(di, bi[r], bi[4 + r], eps2), di, qi[r]);
-            qt0[r] = fma(venkat(d0, bp[r], bp[4 + r], eps2), d0, qp[r]);
+            double pi, p0;
+            venkat2(di, bi + r, d0, bp + r, eps2, pi, p0);
+            qti[r] = fma(pi, di, qi[r]);
+            qt0[r] = fma(p0, d0, qp[r]);
         }
     } else {
 #pragma unroll
@@ -1255,31 +1326,47 @@ __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, doub
     // both directions without branches (an entry outside a direction's
     // stencils gets weight 0), so that the four split-flux evaluations are
     // independent straight-line work the scheduler can interleave
-    double Gs[2][4], Gn[2][4];
-    double ws = 0.0, wn = 0.0;
-    if (M & (kSPlus | kSMinus)) {
-        const bool plus = (f & kSPlus) != 0;
-        const double sg = plus ? 1.0 : -1.0;
-        ws = (f & (kSPlus | kSMinus)) ? fma(ds, plus ? w[0] : w[2], -(dn * (plus ? w[1] : w[3])))
-                                      : 0.0;
-        split_flux(si, tx, ty, sg, Gs[0]);
-        split_flux(s0, tx, ty, sg, Gs[1]);
+    constexpr bool kS = (M & (kSPlus | kSMinus)) != 0, kN = (M & (kNPlus | kNMinus)) != 0;
+    const bool sp = (f & kSPlus) != 0, np = (f & kNPlus) != 0;
+    const double sgs = sp ? 1.0 : -1.0, sgn = np ? 1.0 : -1.0;
+    HalfRange hs[2], hn[2];
+    double far = 0.0;
+    if (kS) {
+        hs[0].near(si, tx, ty, sgs);
+        hs[1].near(s0, tx, ty, sgs);
+        far = fmax(fabs(hs[0].S), fabs(hs[1].S));
     }
-    if (M & (kNPlus | kNMinus)) {
-        const bool plus = (f & kNPlus) != 0;
-        const double sg = plus ? 1.0 : -1.0;
-        wn = (f & (kNPlus | kNMinus)) ? fma(dn, plus ? w[4] : w[6], -(ds * (plus ? w[5] : w[7])))
-                                      : 0.0;
-        split_flux(si, N.x, N.y, sg, Gn[0]);
-        split_flux(s0, N.x, N.y, sg, Gn[1]);
+    if (kN) {
+        hn[0].near(si, N.x, N.y, sgn);
+        hn[1].near(s0, N.x, N.y, sgn);
+        far = fmax(far, fmax(fabs(hn[0].S), fabs(hn[1].S)));
     }
-    if (M & (kSPlus | kSMinus)) {
+    if (far > kErfNear64) {
+        if (kS) {
+            hs[0].far(sgs);
+            hs[1].far(sgs);
+        }
+        if (kN) {
+            hn[0].far(sgn);
+            hn[1].far(sgn);
+        }
+    }
+    double Gi[4], G0[4];
+    if (kS) {
+        const double ws = (f & (kSPlus | kSMinus))
+                              ? fma(ds, sp ? w[0] : w[2], -(dn * (sp ? w[1] : w[3]))) : 0.0;
+        split_flux(si, hs[0], tx, ty, sgs, Gi);
+        split_flux(s0, hs[1], tx, ty, sgs, G0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) R[r] = fma(ws, Gs[0][r] - Gs[1][r], R[r]);
+        for (int r = 0; r < 4; ++r) R[r] = fma(ws, Gi[r] - G0[r], R[r]);
     }
-    if (M & (kNPlus | kNMinus)) {
+    if (kN) {
+        const double wn = (f & (kNPlus | kNMinus))
+                              ? fma(dn, np ? w[4] : w[6], -(ds * (np ? w[5] : w[7]))) : 0.0;
+        split_flux(si, hn[0], N.x, N.y, sgn, Gi);
+        split_flux(s0, hn[1], N.x, N.y, sgn, G0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) R[r] = fma(wn, Gn[0][r] - Gn[1][r], R[r]);
+        for (int r = 0; r < 4; ++r) R[r] = fma(wn, Gi[r] - G0[r], R[r]);
     }
     return ok;
 }
@@ -1307,7 +1394,7 @@ __device__ __forceinline__ bool mirror_entry(double dx, double dy, double2 N, co
         for (int r = 0; r < 4; ++r) qt0[r] = qp[r];
     } else if (LIMITER) {
         const double e = fp.venkat_k * fast_sqrt(fma(mx, mx, my * my));
-        const double eps2 = fmax((e * e) * e, 1e-300);
+        const double eps2 = fmax((e * e) * e, kEps2Min);
         const double hx = -0.5 * mx, hy = -0.5 * my;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1451,7 +1538,6 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
     }
     const int k1 = cl.ptr[p + 1];
     bool ok = true;
-#pragma unroll 2
     for (int k = cl.ptr[p] + sub; k < k1; k += kFluxLanes) {
         const uint8_t f = cl.flag[k] & fmask;
         if (f == 0) continue;

@@ -1,0 +1,44 @@
+"""The FP64 split fluxes on both sides of the line |S| = u_e sqrt(beta) = 1.25
+(local Mach about 1.5) where the flux body changes its form of erfc: states
+that lie below it, across it and far above it, against the oracle.  Each
+component of R within ten times the distance between the oracle's two builds
+(with and without FMA contraction), the bound of the full-size parity tests."""
+import numpy as np
+import pytest
+
+import oracle
+from tests._common import cloud, normwise_rel, smooth_state
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ql():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    from paper_2108_07031_amd import qlskum
+    return qlskum
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("limiter", [0, 1])
+@pytest.mark.parametrize("mach", [0.4, 1.49, 3.0])
+def test_flux_across_the_near_line(ql, mach, limiter, order):
+    print(f"flux body mach={mach} limiter={limiter} order={order}", flush=True)
+    c = cloud("jitter")
+    U = smooth_state(c, mach=mach, alpha_deg=2.0, amp=0.05)
+    prm = dict(mach=mach, alpha_deg=2.0, limiter=limiter, order=order, outer_bc=1)
+    m2 = U[1] ** 2 + U[2] ** 2
+    S = np.sqrt(m2 / (2.0 * U[0] * 0.4 * (U[3] - 0.5 * m2 / U[0])))
+    if mach == 1.49:
+        assert S.min() < 1.25 < S.max()
+    ref = oracle.Oracle(c, oracle.params(**prm)).evaluate(U)["R"]
+    fma = oracle.Oracle(c, oracle.params(**prm), lib=oracle.load(oracle.FMA_LIB)).evaluate(U)["R"]
+    s = ql.Solver(c, **prm)
+    s.set_state(U)
+    R = s.evaluate()["R"]
+    s.close()
+    err, floor = normwise_rel(R, ref), normwise_rel(fma, ref)
+    print("  error", err, "floor", floor, flush=True)
+    assert err.max() <= 10.0 * floor.max()
