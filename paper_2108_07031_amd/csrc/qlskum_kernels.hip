@@ -1467,7 +1467,10 @@ __device__ __forceinline__ bool freestream_flux(const double *u, double2 N, cons
 // on different lanes -- the update was an eighth of the sweep's instructions
 // with one lane of four at work (on 632k points, limiter on: FP64 sweep 307 ->
 // 275 us, mixed 198 -> 179 us).
-// The operations are those of cons_to_q and local_dt, in their order.
+// The operations are those of cons_to_q and local_dt, in their order; the fma
+// of stage 3 takes the product with the new state exactly (in mixed precision
+// another rounding of the update flips single roundings of the FP32 copies of
+// q, and runs then differ at FP32 level).
 __device__ __forceinline__ void quad_update(const DevCloud &cl, const FlowParams &fp, int stage,
                                             int p, int sub, uint8_t kd, double2 N, double R,
                                             double *U, double *Un, double *dt, double2 *qnext,
@@ -1475,7 +1478,7 @@ __device__ __forceinline__ void quad_update(const DevCloud &cl, const FlowParams
 #pragma clang fp contract(off)
     const size_t o = (size_t)sub * cl.n + p;
     double v = fma(-0.5 * dt[p], R, U[o]);
-    if (stage == 3) v = fma(2.0 / 3.0, Un[o], (1.0 / 3.0) * v);
+    if (stage == 3) v = fma(1.0 / 3.0, v, (2.0 / 3.0) * Un[o]);
     double w[4] = {quad_bcast<0>(v), quad_bcast<1>(v), quad_bcast<2>(v), quad_bcast<3>(v)};
     if (kd == kWall) {
         wall_project(w, N);
