@@ -84,8 +84,9 @@ constexpr int kQuadXor2 = 0x4E;  // quad_perm [2, 3, 0, 1]
 template <int CTRL>
 __device__ __forceinline__ double quad_swap(double v) {
     const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, false);
+    // bound_ctrl: no old value to keep, so no register is cleared first
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
@@ -480,30 +481,85 @@ hipError_t launch_prep(hipStream_t st, const DevCloud &c, const FlowParams &fp, 
 // ---------------------------------------------------------------------------
 namespace {
 
-__device__ __forceinline__ double lane_group_max(double v) {
-    v = fmax(v, quad_swap<kQuadXor1>(v));
-    return fmax(v, quad_swap<kQuadXor2>(v));
-}
-
-__device__ __forceinline__ double lane_group_min(double v) {
-    v = fmin(v, quad_swap<kQuadXor1>(v));
-    return fmin(v, quad_swap<kQuadXor2>(v));
-}
-
 template <int CTRL>
-__device__ __forceinline__ float quad_swap_f(float v) {
+__device__ __forceinline__ float quad_swap(float v) {
     return __builtin_bit_cast(
-        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
 
-__device__ __forceinline__ float lane_group_max(float v) {
-    v = fmaxf(v, quad_swap_f<kQuadXor1>(v));
-    return fmaxf(v, quad_swap_f<kQuadXor2>(v));
+// max(a, b) and max(a, -b) as one instruction each (fmax also quiets each
+// operand that the compiler cannot trace to arithmetic, which doubled the
+// sweeps' work on the bounds; a NaN operand loses to a number either way)
+__device__ __forceinline__ double vmax(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double vmax_neg(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, -%2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float vmax(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float vmax_neg(float a, float b) {
+    float r;
+    asm("v_max_f32_e64 %0, %1, -%2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
-__device__ __forceinline__ float lane_group_min(float v) {
-    v = fminf(v, quad_swap_f<kQuadXor1>(v));
-    return fminf(v, quad_swap_f<kQuadXor2>(v));
+// The sweeps' results per point are eight values in four pairs, and lane sub
+// ends with pair sub: the lanes exchange the halves that the partner keeps, so
+// that a reduction costs one exchange per kept value instead of one per value.
+// These ends of the sweeps were most of their instructions (first pass: 500 of
+// 623 per wave) while every lane reduced and selected all eight values.
+
+// Components 2 (sub & 1), 2 (sub & 1) + 1 of lane_group_sum, in its order.
+__device__ __forceinline__ void lane_group_sum_pair(const double v[4], int sub, double out[2]) {
+    const bool odd = (sub & 1) != 0;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const double t = (odd ? v[2 + m] : v[m]) + quad_swap<kQuadXor1>(odd ? v[m] : v[2 + m]);
+        out[m] = t + quad_swap<kQuadXor2>(t);
+    }
+}
+
+// Pair sub of (max, min) over the lanes, mx holding the lanes' maxima and mg
+// the maxima of the negated values (max is exact in any order).
+template <class T>
+__device__ __forceinline__ void lane_group_bounds_pair(const T mx[4], const T mg[4], int sub,
+                                                       T out[2]) {
+    const bool odd = (sub & 1) != 0, low = sub >= 2;  // lanes 2, 3: the minima
+    T t[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        t[r] = vmax(low ? mg[r] : mx[r], quad_swap<kQuadXor2>(low ? mx[r] : mg[r]));
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const T u = vmax(odd ? t[2 + m] : t[m], quad_swap<kQuadXor1>(odd ? t[m] : t[2 + m]));
+        out[m] = low ? -u : u;
+    }
+}
+
+// Pair sub of the least-squares solve L (sx, sy) (rows q_x: lanes 0, 1; q_y:
+// lanes 2, 3).
+__device__ __forceinline__ void solve_pair(const double *lsi, int p, const double sx[4],
+                                           const double sy[4], int sub, double out[2]) {
+    const bool y = sub >= 2;
+    const double L0 = lsi[3 * (size_t)p + (y ? 2 : 0)], L1 = lsi[3 * (size_t)p + 1];
+    double ax[2], ay[2];
+    lane_group_sum_pair(sx, sub, ax);
+    lane_group_sum_pair(sy, sub, ay);
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+        out[m] = fma(L0, y ? ay[m] : ax[m], -(L1 * (y ? ax[m] : ay[m])));
+}
+
+__device__ __forceinline__ void store_pair(float4 *a, int p, int sub, double v0, double v1) {
+    reinterpret_cast<float2 *>(a)[4 * (size_t)p + sub] = make_float2((float)v0, (float)v1);
 }
 
 // tile set-up shared by the tiled sweeps: image size ns and whether it is
@@ -540,13 +596,13 @@ __device__ __forceinline__ int slot_point(const DevCloud &cl, const TileInfo &ti
 // from either would be compiled to generic (flat) loads, which go through
 // the vector-memory path even for LDS and wait on both counters.
 
-// first pass: sums of dx dq, dy dq and the componentwise max / min over the
-// entries k0 + sub, k0 + sub + kFluxLanes, ... < k1 of point p
+// first pass: sums of dx dq, dy dq and the componentwise maxima of q and -q
+// over the entries k0 + sub, k0 + sub + kFluxLanes, ... < k1 of point p
 template <bool LDS>
 __device__ __forceinline__ void grad0_entries(const DevCloud &cl, const double2 *lds,
                                               const double2 *q, int k0, int k1, int sub,
                                               const double qp[4], double2 P, double sx[4],
-                                              double sy[4], double mx[4], double mn[4]) {
+                                              double sy[4], double mx[4], double mg[4]) {
     constexpr int kRec = 3;
     for (int k = k0 + sub; k < k1; k += kFluxLanes) {
         double qi[4];
@@ -566,8 +622,8 @@ __device__ __forceinline__ void grad0_entries(const DevCloud &cl, const double2 
             const double dq = qi[r] - qp[r];
             sx[r] = fma(dx, dq, sx[r]);
             sy[r] = fma(dy, dq, sy[r]);
-            mx[r] = fmax(mx[r], qi[r]);
-            mn[r] = fmin(mn[r], qi[r]);
+            mx[r] = vmax(mx[r], qi[r]);
+            mg[r] = vmax_neg(mg[r], qi[r]);
         }
     }
 }
@@ -604,9 +660,8 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
     const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
     const int p = ti.base + j;
     double sx[4] = {0, 0, 0, 0}, sy[4] = {0, 0, 0, 0};
-    double mx[4] = {0, 0, 0, 0}, mn[4] = {0, 0, 0, 0};
+    double mx[4] = {0, 0, 0, 0}, mg[4] = {0, 0, 0, 0}, qp[4] = {0, 0, 0, 0};
     if (j < ti.nown) {
-        double qp[4];
         // the own position from memory on both paths (one load per point; a
         // value that may come from LDS or memory would be a generic load)
         const double2 P = cl.xy[p];
@@ -617,49 +672,30 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
             load4(q, p, qp);
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) mx[r] = mn[r] = qp[r];
+        for (int r = 0; r < 4; ++r) {
+            mx[r] = qp[r];
+            mg[r] = -qp[r];
+        }
         const int k0 = cl.ptr[p], k1 = cl.ptr[p + 1];
         if (ti.in_lds)
-            grad0_entries<true>(cl, lds, q, k0, k1, sub, qp, P, sx, sy, mx, mn);
+            grad0_entries<true>(cl, lds, q, k0, k1, sub, qp, P, sx, sy, mx, mg);
         else
-            grad0_entries<false>(cl, lds, q, k0, k1, sub, qp, P, sx, sy, mx, mn);
+            grad0_entries<false>(cl, lds, q, k0, k1, sub, qp, P, sx, sy, mx, mg);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        sx[r] = lane_group_sum(sx[r]);
-        sy[r] = lane_group_sum(sy[r]);
-        mx[r] = lane_group_max(mx[r]);
-        mn[r] = lane_group_min(mn[r]);
-    }
-    if (j >= ti.nown) return;
-    const double L0 = cl.lsi[3 * p], L1 = cl.lsi[3 * p + 1], L2 = cl.lsi[3 * p + 2];
-    double gv[8];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        gv[r] = fma(L0, sx[r], -(L1 * sy[r]));
-        gv[4 + r] = fma(L2, sy[r], -(L1 * sx[r]));
-    }
-    // each of the point's lanes stores one 16-byte part
-    g[4 * p + sub] = make_double2(gv[2 * sub], gv[2 * sub + 1]);
-    if (sh.g32 && sub < 2) sh.g32[2 * p + sub] = to_f4(gv + 4 * sub);
+    if (j >= ti.nown) return;  // whole groups of lanes leave
+    double gv[2];
+    solve_pair(cl.lsi, p, sx, sy, sub, gv);
+    g[4 * (size_t)p + sub] = make_double2(gv[0], gv[1]);
+    if (sh.g32) store_pair(sh.g32, p, sub, gv[0], gv[1]);
     if (want_bounds) {
         // bounds are stored as offsets from q (the limiter's D = q_max - q or
         // q_min - q, the same FP64 subtraction it would make per entry)
-        double qp[4];
-        if (ti.in_lds) {
-            const double2 *r = lds + kRec * j;
-            qp[0] = r[0].x; qp[1] = r[0].y; qp[2] = r[1].x; qp[3] = r[1].y;
-        } else {
-            load4(q, p, qp);
-        }
-        double bv[8];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            bv[r] = mx[r] - qp[r];
-            bv[4 + r] = mn[r] - qp[r];
-        }
-        if (B64) qmm[4 * p + sub] = make_double2(bv[2 * sub], bv[2 * sub + 1]);
-        if (sh.qmm32 && sub < 2) sh.qmm32[2 * p + sub] = to_f4(bv + 4 * sub);
+        double bv[2];
+        lane_group_bounds_pair(mx, mg, sub, bv);
+        bv[0] -= (sub & 1) ? qp[2] : qp[0];
+        bv[1] -= (sub & 1) ? qp[3] : qp[1];
+        if (B64) qmm[4 * (size_t)p + sub] = make_double2(bv[0], bv[1]);
+        if (sh.qmm32) store_pair(sh.qmm32, p, sub, bv[0], bv[1]);
     }
 }
 
@@ -724,14 +760,10 @@ __global__ void __launch_bounds__(kBlock) k_gradk(DevCloud cl, int cap,
     const int p = ti.base + j;
     const bool own = j < ti.nown;
     int kb = 0, k1 = 0;
-    double L0 = 0.0, L1 = 0.0, L2 = 0.0;
     double2 z = make_double2(0.0, 0.0), gq = make_double2(0.0, 0.0);
     if (own) {
         kb = cl.ptr[p];
         k1 = cl.ptr[p + 1];
-        L0 = cl.lsi[3 * p];
-        L1 = cl.lsi[3 * p + 1];
-        L2 = cl.lsi[3 * p + 2];
         z = g0[4 * p + sub];
         gq = gprev[4 * p + sub];
     }
@@ -770,29 +802,12 @@ __global__ void __launch_bounds__(kBlock) k_gradk(DevCloud cl, int cap,
         else
             gradk_entries<2>(cl, lds, eidx, e0, gprev, kb, k1, sub, P, sx, sy);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        sx[r] = lane_group_sum(sx[r]);
-        sy[r] = lane_group_sum(sy[r]);
-    }
-    if (!own) return;
-    // lane sub produces components 2 sub, 2 sub + 1 of (q_x[0..3], q_y[0..3])
-    double v[2];
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int c = 2 * sub + m, r = c & 3;
-        const double ls = (c < 4) ? fma(L0, sx[r], -(L1 * sy[r])) : fma(L2, sy[r], -(L1 * sx[r]));
-        v[m] = fma(-0.5, ls - (m == 0 ? gq.x : gq.y), m == 0 ? z.x : z.y);
-    }
-    if (gnext) gnext[4 * p + sub] = make_double2(v[0], v[1]);
-    if (g32) {
-        // the FP32 shadow packs (q_x[0..3]) and (q_y[0..3]): lanes 0,1 and 2,3
-        // hold halves of one float4, combined through a shuffle of partner lanes
-        const double o0 = quad_swap<kQuadXor1>(v[0]), o1 = quad_swap<kQuadXor1>(v[1]);
-        if ((sub & 1) == 0)
-            g32[2 * p + (sub >> 1)] =
-                make_float4((float)v[0], (float)v[1], (float)o0, (float)o1);
-    }
+    if (!own) return;  // whole groups of lanes leave
+    double ls[2];
+    solve_pair(cl.lsi, p, sx, sy, sub, ls);
+    const double v0 = fma(-0.5, ls[0] - gq.x, z.x), v1 = fma(-0.5, ls[1] - gq.y, z.y);
+    if (gnext) gnext[4 * (size_t)p + sub] = make_double2(v0, v1);
+    if (g32) store_pair(g32, p, sub, v0, v1);
 }
 
 // ---------------------------------------------------------------------------
@@ -815,7 +830,7 @@ template <int SRC>
 __device__ __forceinline__ void grad0f_entries(const DevCloud &cl, const double2 *lds,
                                                const float4 *q32, int k0, int k1, int sub,
                                                const double qp[4], double2 P, double sx[4],
-                                               double sy[4], float mx[4], float mn[4]) {
+                                               double sy[4], float mx[4], float mg[4]) {
     constexpr int kRec = 2;
     // two entries in flight per lane (each lane's sums keep their order)
 #pragma unroll 2
@@ -839,8 +854,8 @@ __device__ __forceinline__ void grad0f_entries(const DevCloud &cl, const double2
             const double dq = (double)qf[r] - qp[r];
             sx[r] = fma(dx, dq, sx[r]);
             sy[r] = fma(dy, dq, sy[r]);
-            mx[r] = fmaxf(mx[r], qf[r]);
-            mn[r] = fminf(mn[r], qf[r]);
+            mx[r] = vmax(mx[r], qf[r]);
+            mg[r] = vmax_neg(mg[r], qf[r]);
         }
     }
 }
@@ -912,42 +927,33 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
     const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
     const int p = ti.base + j;
     double sx[4] = {0, 0, 0, 0}, sy[4] = {0, 0, 0, 0};
-    float mx[4] = {0, 0, 0, 0}, mn[4] = {0, 0, 0, 0};
+    float mx[4] = {0, 0, 0, 0}, mg[4] = {0, 0, 0, 0};
     double qp[4] = {0, 0, 0, 0};
     if (j < ti.nown) {
         const float4 a = q32[p];
         f4_to_d(a, qp);
         const double2 P = cl.xy[p];
-        mx[0] = mn[0] = a.x;
-        mx[1] = mn[1] = a.y;
-        mx[2] = mn[2] = a.z;
-        mx[3] = mn[3] = a.w;
+        const float qf[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            mx[r] = qf[r];
+            mg[r] = -qf[r];
+        }
         const int k0 = cl.ptr[p], k1 = cl.ptr[p + 1];
         if (ti.in_lds)
-            grad0f_entries<0>(cl, lds, q32, k0, k1, sub, qp, P, sx, sy, mx, mn);
+            grad0f_entries<0>(cl, lds, q32, k0, k1, sub, qp, P, sx, sy, mx, mg);
         else
-            grad0f_entries<2>(cl, lds, q32, k0, k1, sub, qp, P, sx, sy, mx, mn);
+            grad0f_entries<2>(cl, lds, q32, k0, k1, sub, qp, P, sx, sy, mx, mg);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        sx[r] = lane_group_sum(sx[r]);
-        sy[r] = lane_group_sum(sy[r]);
-        mx[r] = lane_group_max(mx[r]);
-        mn[r] = lane_group_min(mn[r]);
-    }
-    if (j >= ti.nown || sub >= 2) return;
-    const double L0 = cl.lsi[3 * p], L1 = cl.lsi[3 * p + 1], L2 = cl.lsi[3 * p + 2];
-    double gv[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        gv[r] = (sub == 0) ? fma(L0, sx[r], -(L1 * sy[r])) : fma(L2, sy[r], -(L1 * sx[r]));
-    g0f[2 * p + sub] = to_f4(gv);
+    if (j >= ti.nown) return;  // whole groups of lanes leave
+    double gv[2];
+    solve_pair(cl.lsi, p, sx, sy, sub, gv);
+    store_pair(g0f, p, sub, gv[0], gv[1]);
     if (want_bounds) {
-        // bound offsets from q: lane 0 the maxima, lane 1 the minima
-        double bv[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bv[r] = (double)(sub == 0 ? mx[r] : mn[r]) - qp[r];
-        qmm32[2 * p + sub] = to_f4(bv);
+        float bv[2];  // bound offsets from q
+        lane_group_bounds_pair(mx, mg, sub, bv);
+        store_pair(qmm32, p, sub, (double)bv[0] - ((sub & 1) ? qp[2] : qp[0]),
+                   (double)bv[1] - ((sub & 1) ? qp[3] : qp[1]));
     }
 }
 
@@ -965,14 +971,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))
     const int p = ti.base + j;
     const bool own = j < ti.nown;
     int kb = 0, k1 = 0;
-    double L0 = 0.0, L1 = 0.0, L2 = 0.0;
     double2 z = make_double2(0.0, 0.0), gq = make_double2(0.0, 0.0);
     if (own) {
         kb = cl.ptr[p];
         k1 = cl.ptr[p + 1];
-        L0 = cl.lsi[3 * p];
-        L1 = cl.lsi[3 * p + 1];
-        L2 = cl.lsi[3 * p + 2];
         z = lane_pair(g0f, p, sub);
         gq = lane_pair(gprev, p, sub);
     }
@@ -1004,23 +1006,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))
         else
             gradkf_entries<2>(cl, lds, eidx, e0, gprev, kb, k1, sub, P, sx, sy);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        sx[r] = lane_group_sum(sx[r]);
-        sy[r] = lane_group_sum(sy[r]);
-    }
-    if (!own) return;
-    double v[2];
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int c = 2 * sub + m, r = c & 3;
-        const double ls = (c < 4) ? fma(L0, sx[r], -(L1 * sy[r])) : fma(L2, sy[r], -(L1 * sx[r]));
-        v[m] = fma(-0.5, ls - (m == 0 ? gq.x : gq.y), m == 0 ? z.x : z.y);
-    }
-    // lanes 0,1 and 2,3 hold halves of one float4 (see k_gradk)
-    const double o0 = quad_swap<kQuadXor1>(v[0]), o1 = quad_swap<kQuadXor1>(v[1]);
-    if ((sub & 1) == 0)
-        gnext[2 * p + (sub >> 1)] = make_float4((float)v[0], (float)v[1], (float)o0, (float)o1);
+    if (!own) return;  // whole groups of lanes leave
+    double ls[2];
+    solve_pair(cl.lsi, p, sx, sy, sub, ls);
+    store_pair(gnext, p, sub, fma(-0.5, ls[0] - gq.x, z.x), fma(-0.5, ls[1] - gq.y, z.y));
 }
 
 static int lds_cap(const DevCloud &c, int budget, int rec) {
