@@ -545,17 +545,23 @@ __device__ __forceinline__ void lane_group_bounds_pair(const T mx[4], const T mg
 }
 
 // Pair sub of the least-squares solve L (sx, sy) (rows q_x: lanes 0, 1; q_y:
-// lanes 2, 3).
-__device__ __forceinline__ void solve_pair(const double *lsi, int p, const double sx[4],
-                                           const double sy[4], int sub, double out[2]) {
+// lanes 2, 3) with the factors of the lane's row, read early by load_row.
+struct LsRow {
+    double L0 = 0.0, L1 = 0.0;
+    __device__ __forceinline__ void load_row(const double *lsi, int p, int sub) {
+        L0 = lsi[3 * (size_t)p + (sub & 2)];
+        L1 = lsi[3 * (size_t)p + 1];
+    }
+};
+__device__ __forceinline__ void solve_pair(const LsRow &w, const double sx[4], const double sy[4],
+                                           int sub, double out[2]) {
     const bool y = sub >= 2;
-    const double L0 = lsi[3 * (size_t)p + (y ? 2 : 0)], L1 = lsi[3 * (size_t)p + 1];
     double ax[2], ay[2];
     lane_group_sum_pair(sx, sub, ax);
     lane_group_sum_pair(sy, sub, ay);
 #pragma unroll
     for (int m = 0; m < 2; ++m)
-        out[m] = fma(L0, y ? ay[m] : ax[m], -(L1 * (y ? ax[m] : ay[m])));
+        out[m] = fma(w.L0, y ? ay[m] : ax[m], -(w.L1 * (y ? ax[m] : ay[m])));
 }
 
 __device__ __forceinline__ void store_pair(float4 *a, int p, int sub, double v0, double v1) {
@@ -645,6 +651,20 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
     const int t = sweep_tile(cl);
     if (cl.tile_active && !cl.tile_active[t]) return;
     const TileInfo ti = tile_info(cl, t, cap);
+    const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
+    const int p = ti.base + j;
+    // the point's own data, read while the image is staged (its position from
+    // memory on both paths: a value that may come from LDS or memory would be a
+    // generic load)
+    int k0 = 0, k1 = 0;
+    double2 P = make_double2(0.0, 0.0);
+    LsRow L;
+    if (j < ti.nown) {
+        k0 = cl.ptr[p];
+        k1 = cl.ptr[p + 1];
+        P = cl.xy[p];
+        L.load_row(cl.lsi, p, sub);
+    }
     if (ti.in_lds) {
         for (int s0 = threadIdx.x; s0 < ti.ns; s0 += kBlock) {
             const int p0 = slot_point(cl, ti, s0);
@@ -657,14 +677,9 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
         }
     }
     __syncthreads();
-    const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
-    const int p = ti.base + j;
     double sx[4] = {0, 0, 0, 0}, sy[4] = {0, 0, 0, 0};
     double mx[4] = {0, 0, 0, 0}, mg[4] = {0, 0, 0, 0}, qp[4] = {0, 0, 0, 0};
     if (j < ti.nown) {
-        // the own position from memory on both paths (one load per point; a
-        // value that may come from LDS or memory would be a generic load)
-        const double2 P = cl.xy[p];
         if (ti.in_lds) {
             const double2 *r = lds + kRec * j;
             qp[0] = r[0].x; qp[1] = r[0].y; qp[2] = r[1].x; qp[3] = r[1].y;
@@ -676,7 +691,6 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
             mx[r] = qp[r];
             mg[r] = -qp[r];
         }
-        const int k0 = cl.ptr[p], k1 = cl.ptr[p + 1];
         if (ti.in_lds)
             grad0_entries<true>(cl, lds, q, k0, k1, sub, qp, P, sx, sy, mx, mg);
         else
@@ -684,7 +698,7 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
     }
     if (j >= ti.nown) return;  // whole groups of lanes leave
     double gv[2];
-    solve_pair(cl.lsi, p, sx, sy, sub, gv);
+    solve_pair(L, sx, sy, sub, gv);
     g[4 * (size_t)p + sub] = make_double2(gv[0], gv[1]);
     if (sh.g32) store_pair(sh.g32, p, sub, gv[0], gv[1]);
     if (want_bounds) {
@@ -702,6 +716,17 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
 // entry slots an inner-iteration workgroup stages in LDS (tiles with more
 // entries read them from memory)
 constexpr int kCapE = 2048;
+
+// The tile's entry slots flidx[e0 .. e0 + ne), copied into LDS in 16-byte
+// chunks from the chunk that holds e0 (one load per lane for a tile of 64
+// 24-entry points, where single slots took six dependent rounds); entry k is
+// then at eidx[k - e0a].  The array is padded to a whole chunk.
+__device__ __forceinline__ int entry_origin(int e0) { return e0 & ~7; }
+__device__ __forceinline__ void stage_entries(const DevCloud &cl, uint16_t *eidx, int e0, int ne) {
+    const int e0a = entry_origin(e0), nc = (e0 + ne - e0a + 7) / 8;
+    const uint4 *src = reinterpret_cast<const uint4 *>(cl.flidx + e0a);
+    for (int c = threadIdx.x; c < nc; c += kBlock) reinterpret_cast<uint4 *>(eidx)[c] = src[c];
+}
 constexpr int kLdsBytes = 160 * 1024;  // LDS one workgroup may allocate on gfx950
 
 // inner iteration: sums of dx f, dy f with f = dx g_x,i + dy g_y,i over the
@@ -760,15 +785,20 @@ __global__ void __launch_bounds__(kBlock) k_gradk(DevCloud cl, int cap,
     const int p = ti.base + j;
     const bool own = j < ti.nown;
     int kb = 0, k1 = 0;
-    double2 z = make_double2(0.0, 0.0), gq = make_double2(0.0, 0.0);
+    double2 z = make_double2(0.0, 0.0), gq = z, P = z;
+    LsRow L;
     if (own) {
         kb = cl.ptr[p];
         k1 = cl.ptr[p + 1];
+        L.load_row(cl.lsi, p, sub);
+        P = cl.xy[p];
         z = g0[4 * p + sub];
         gq = gprev[4 * p + sub];
     }
     const int e0 = cl.ptr[ti.base], ne = cl.ptr[ti.base + ti.nown] - e0;
-    const bool e_lds = ti.in_lds && ne <= kCapE;
+    const int e0a = entry_origin(e0);
+    const bool e_lds = ti.in_lds && e0 + ne - e0a <= kCapE;
+    if (e_lds) stage_entries(cl, eidx, e0, ne);
     if (ti.in_lds) {
         for (int s0 = threadIdx.x; s0 < ti.ns; s0 += 2 * kBlock) {
             const int s1 = s0 + kBlock;
@@ -788,23 +818,20 @@ __global__ void __launch_bounds__(kBlock) k_gradk(DevCloud cl, int cap,
                 d[0] = b0; d[1] = b1; d[2] = b2; d[3] = b3; d[4] = b4;
             }
         }
-        if (e_lds)
-            for (int e = threadIdx.x; e < ne; e += kBlock) eidx[e] = cl.flidx[e0 + e];
     }
     __syncthreads();
     double sx[4] = {0, 0, 0, 0}, sy[4] = {0, 0, 0, 0};
     if (own) {
-        const double2 P = cl.xy[p];  // from memory on both paths (see k_grad0)
         if (e_lds)
-            gradk_entries<0>(cl, lds, eidx, e0, gprev, kb, k1, sub, P, sx, sy);
+            gradk_entries<0>(cl, lds, eidx, e0a, gprev, kb, k1, sub, P, sx, sy);
         else if (ti.in_lds)
-            gradk_entries<1>(cl, lds, eidx, e0, gprev, kb, k1, sub, P, sx, sy);
+            gradk_entries<1>(cl, lds, eidx, e0a, gprev, kb, k1, sub, P, sx, sy);
         else
-            gradk_entries<2>(cl, lds, eidx, e0, gprev, kb, k1, sub, P, sx, sy);
+            gradk_entries<2>(cl, lds, eidx, e0a, gprev, kb, k1, sub, P, sx, sy);
     }
     if (!own) return;  // whole groups of lanes leave
     double ls[2];
-    solve_pair(cl.lsi, p, sx, sy, sub, ls);
+    solve_pair(L, sx, sy, sub, ls);
     const double v0 = fma(-0.5, ls[0] - gq.x, z.x), v1 = fma(-0.5, ls[1] - gq.y, z.y);
     if (gnext) gnext[4 * (size_t)p + sub] = make_double2(v0, v1);
     if (g32) store_pair(g32, p, sub, v0, v1);
@@ -912,6 +939,20 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
     const int t = sweep_tile(cl);
     if (cl.tile_active && !cl.tile_active[t]) return;
     const TileInfo ti = tile_info(cl, t, cap);
+    const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
+    const int p = ti.base + j;
+    // the point's own data, read while the image is staged
+    int k0 = 0, k1 = 0;
+    double2 P = make_double2(0.0, 0.0);
+    float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    LsRow L;
+    if (j < ti.nown) {
+        k0 = cl.ptr[p];
+        k1 = cl.ptr[p + 1];
+        P = cl.xy[p];
+        a = q32[p];
+        L.load_row(cl.lsi, p, sub);
+    }
     if (ti.in_lds) {
         for (int s0 = threadIdx.x; s0 < ti.ns; s0 += kBlock) {
             const int p0 = slot_point(cl, ti, s0);
@@ -924,22 +965,17 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
         }
     }
     __syncthreads();
-    const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
-    const int p = ti.base + j;
     double sx[4] = {0, 0, 0, 0}, sy[4] = {0, 0, 0, 0};
     float mx[4] = {0, 0, 0, 0}, mg[4] = {0, 0, 0, 0};
     double qp[4] = {0, 0, 0, 0};
     if (j < ti.nown) {
-        const float4 a = q32[p];
         f4_to_d(a, qp);
-        const double2 P = cl.xy[p];
         const float qf[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             mx[r] = qf[r];
             mg[r] = -qf[r];
         }
-        const int k0 = cl.ptr[p], k1 = cl.ptr[p + 1];
         if (ti.in_lds)
             grad0f_entries<0>(cl, lds, q32, k0, k1, sub, qp, P, sx, sy, mx, mg);
         else
@@ -947,7 +983,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
     }
     if (j >= ti.nown) return;  // whole groups of lanes leave
     double gv[2];
-    solve_pair(cl.lsi, p, sx, sy, sub, gv);
+    solve_pair(L, sx, sy, sub, gv);
     store_pair(g0f, p, sub, gv[0], gv[1]);
     if (want_bounds) {
         float bv[2];  // bound offsets from q
@@ -971,15 +1007,20 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))
     const int p = ti.base + j;
     const bool own = j < ti.nown;
     int kb = 0, k1 = 0;
-    double2 z = make_double2(0.0, 0.0), gq = make_double2(0.0, 0.0);
+    double2 z = make_double2(0.0, 0.0), gq = z, P = z;
+    LsRow L;
     if (own) {
         kb = cl.ptr[p];
         k1 = cl.ptr[p + 1];
+        L.load_row(cl.lsi, p, sub);
+        P = cl.xy[p];
         z = lane_pair(g0f, p, sub);
         gq = lane_pair(gprev, p, sub);
     }
     const int e0 = cl.ptr[ti.base], ne = cl.ptr[ti.base + ti.nown] - e0;
-    const bool e_lds = ti.in_lds && ne <= kCapE;
+    const int e0a = entry_origin(e0);
+    const bool e_lds = ti.in_lds && e0 + ne - e0a <= kCapE;
+    if (e_lds) stage_entries(cl, eidx, e0, ne);
     if (ti.in_lds) {
         for (int s0 = threadIdx.x; s0 < ti.ns; s0 += kBlock) {
             const int p0 = slot_point(cl, ti, s0);
@@ -992,23 +1033,20 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))
                 d[2] = a2;
             }
         }
-        if (e_lds)
-            for (int e = threadIdx.x; e < ne; e += kBlock) eidx[e] = cl.flidx[e0 + e];
     }
     __syncthreads();
     double sx[4] = {0, 0, 0, 0}, sy[4] = {0, 0, 0, 0};
     if (own) {
-        const double2 P = cl.xy[p];
         if (e_lds)
-            gradkf_entries<0>(cl, lds, eidx, e0, gprev, kb, k1, sub, P, sx, sy);
+            gradkf_entries<0>(cl, lds, eidx, e0a, gprev, kb, k1, sub, P, sx, sy);
         else if (ti.in_lds)
-            gradkf_entries<1>(cl, lds, eidx, e0, gprev, kb, k1, sub, P, sx, sy);
+            gradkf_entries<1>(cl, lds, eidx, e0a, gprev, kb, k1, sub, P, sx, sy);
         else
-            gradkf_entries<2>(cl, lds, eidx, e0, gprev, kb, k1, sub, P, sx, sy);
+            gradkf_entries<2>(cl, lds, eidx, e0a, gprev, kb, k1, sub, P, sx, sy);
     }
     if (!own) return;  // whole groups of lanes leave
     double ls[2];
-    solve_pair(cl.lsi, p, sx, sy, sub, ls);
+    solve_pair(L, sx, sy, sub, ls);
     store_pair(gnext, p, sub, fma(-0.5, ls[0] - gq.x, z.x), fma(-0.5, ls[1] - gq.y, z.y));
 }
 

@@ -1042,7 +1042,8 @@ static int upload_impl(ql_solver *s, int32_t ncase, const int64_t *case_ptr, int
                 s->fslots[t] = kFluxTile + thptr[t + 1] - thptr[t];
             HIPCHK(s, dalloc(&s->fhalo_ptr, thptr.size()));
             HIPCHK(s, dalloc(&s->fhalo_idx, thidx.size()));
-            HIPCHK(s, dalloc(&s->flidx, tlidx.size()));
+            // read in 16-byte chunks of eight slots
+            HIPCHK(s, dalloc(&s->flidx, (tlidx.size() + 7) / 8 * 8));
             HIPCHK(s, hipMemcpy(s->fhalo_ptr, thptr.data(), sizeof(int) * thptr.size(),
                                 hipMemcpyHostToDevice));
             if (!thidx.empty())
