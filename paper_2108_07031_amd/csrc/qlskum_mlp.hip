@@ -292,20 +292,24 @@ hipError_t launch_colsum(hipStream_t st, int64_t n, int w, const bf16 *d, float 
     return hipGetLastError();
 }
 
-// Adam (Kingma and Ba, 2015) on the FP32 master weights with bias-corrected
-// moments: c1 = 1/(1 - beta1^t), c2 = 1/(1 - beta2^t).
+// Adam (Kingma and Ba, 2015) on one FP32 master weight with bias-corrected
+// moments: c1 = 1/(1 - beta1^t), c2 = 1/(1 - beta2^t).  Returns the new weight.
+__device__ __forceinline__ float adam_step(float gi, float lr, float b1, float b2, float eps,
+                                           float c1, float c2, float *w, float *m, float *v) {
+    const float mi = b1 * *m + (1.0f - b1) * gi;
+    const float vi = b2 * *v + (1.0f - b2) * gi * gi;
+    *m = mi;
+    *v = vi;
+    return *w = *w - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+}
+
 __global__ void __launch_bounds__(256) k_adam(int np, float lr, float b1, float b2, float eps,
                                               float c1, float c2, const float *__restrict__ g,
                                               float *__restrict__ w, float *__restrict__ m,
                                               float *__restrict__ v) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= np) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    w[i] = w[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+    adam_step(g[i], lr, b1, b2, eps, c1, c2, w + i, m + i, v + i);
 }
 
 hipError_t launch_adam(hipStream_t st, int np, float lr, float b1, float b2, float eps, float c1,
@@ -332,6 +336,412 @@ hipError_t launch_weights_bf16(hipStream_t st, int fi, int fo, const float *W, b
                                bf16 *WbT) {
     hipLaunchKernelGGL(k_weights_bf16, dim3((fi * fo + 255) / 256), dim3(256), 0, st, fi, fo, W,
                        Wb, WbT);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Fused path.  The products, their order along the inner dimension and every
+// rounding are those of the kernels above, so a network's outputs and gradients
+// do not depend on the path.
+// ---------------------------------------------------------------------------
+namespace {
+
+constexpr int kLd = kFuseWidth + 8;  // LDS row: 272 bytes, 16 rows on distinct banks
+constexpr int kFrag = 16 * 32;       // elements of a fragment
+
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// Place of element (column c, inner index k) among fragments of `steps` steps
+// per 16 columns: lane 16 (k % 32 / 8) + c % 16 holds eight consecutive k.
+__device__ __forceinline__ size_t frag_index(int c, int k, int steps) {
+    return ((size_t)(c >> 4) * steps + (k >> 5)) * kFrag + (((k >> 3) & 3) * 16 + (c & 15)) * 8 +
+           (k & 7);
+}
+
+// 16 x 16 block: rows of A in LDS (leading dimension kLd, zero past K), columns
+// b of B, K in ks steps of 32
+__device__ __forceinline__ f32x4 block_product(const bf16 *A, const bf16x8 b[4], int ks, int lane) {
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    const bf16 *r = A + (lane & 15) * kLd + 8 * (lane >> 4);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+        if (s < ks)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                *reinterpret_cast<const bf16x8 *>(r + 32 * s), b[s], acc, 0, 0, 0);
+    return acc;
+}
+
+}  // namespace
+
+// MB blocks of 16 rows through all layers: bf16 activations in LDS, NW
+// wavefronts sharing a layer's 16-column blocks, the weights' fragments read
+// from L2 once per row tile, a layer's first ones while the layer before ends.
+// Bound by tanh: 6-128x4-4 inference needs 512 of them a row against 51k
+// multiply-adds on the matrix cores.  640,000 rows 279 us; layer by layer it took
+// six kernels per max_batch rows, with every activation through memory twice
+// (2033 us).
+// TRAIN: the same, then the output error and the errors of every layer back to
+// the first (each row's own).  a_l and d_l are left in memory as fragments along
+// the batch, zero past row n: a lane's four results are consecutive rows of one
+// column, and the wavefront's 8-byte stores fill 512 bytes in a row.
+template <int MB, int NW, bool TRAIN>
+__global__ void __launch_bounds__(64 * NW)
+    k_mlp_rows(MlpNet net, int64_t n, const float *__restrict__ X, const float *__restrict__ T,
+               float *__restrict__ Y, float scale, float *__restrict__ losspart) {
+    constexpr int MT = 16 * MB;
+    extern __shared__ __align__(16) bf16 sm[];
+    auto buf = [&](int i) { return sm + i * MT * kLd; };
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 15, mq = 4 * (lane >> 4);
+    const int64_t r0 = (int64_t)blockIdx.x * MT;
+    const int rows = (int)max((int64_t)0, min((int64_t)MT, n - r0));
+    // this wavefront's block t of step s: the forward layers 0 .. L-1, then the
+    // layers L-1 .. 1 backward
+    auto fetch = [&](int s, int t, bf16x8 b[4], float &bias) {
+        const bool fwd = s < net.L;
+        const int l = fwd ? s : 2 * net.L - 1 - s;
+        const int K = net.w[fwd ? l : l + 1], N = net.w[fwd ? l + 1 : l], c = 16 * t + col;
+        const int ks = (K + 31) / 32;
+        const bf16 *P = (fwd ? net.Wf[l] : net.Wr[l]) + (size_t)t * ks * kFrag + 8 * lane;
+        if (16 * t < mlp_pad(N)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < ks) b[k] = *reinterpret_cast<const bf16x8 *>(P + k * kFrag);
+        }
+        bias = (fwd && c < N) ? net.wt[net.woff[l] + K * N + c] : 0.0f;
+    };
+    // rows m .. m + 3 of column c into a batch fragment array, zero past row n
+    auto put = [&](bf16 *P, int m, int c, bf16x4 v) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (m + i >= rows) v[i] = (bf16)0.0f;
+        *reinterpret_cast<bf16x4 *>(P + frag_index(c, (int)(r0 + m), net.steps)) = v;
+    };
+    bf16x8 b[4];
+    float bias;
+    fetch(0, wave, b, bias);
+    const int w0 = net.w[0], w0p = mlp_pad(w0);
+    for (int e = threadIdx.x; e < MT * w0p; e += 64 * NW) {
+        const int m = e / w0p, c = e - m * w0p;
+        buf(0)[m * kLd + c] = (m < rows && c < w0) ? (bf16)X[(r0 + m) * w0 + c] : (bf16)0.0f;
+    }
+    __syncthreads();
+    if (TRAIN) {
+        for (int e = threadIdx.x; e < MT / 4 * w0p; e += 64 * NW) {
+            const int m = e / w0p * 4, c = e % w0p;
+            bf16x4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = buf(0)[(m + i) * kLd + c];
+            put(net.aT[0], m, c, v);
+        }
+    }
+    float e2 = 0.0f;
+    for (int l = 0; l < net.L; ++l) {
+        const int fi = net.w[l], fo = net.w[l + 1], ks = (fi + 31) / 32;
+        const bool last = l + 1 == net.L;
+        const bf16 *in = buf(TRAIN ? l : l & 1);
+        bf16 *out = buf(TRAIN ? l + 1 : (l + 1) & 1);
+        const int nt = last && !TRAIN ? (fo + 15) / 16 : mlp_pad(fo) / 16;
+        for (int t = wave; t < nt; t += NW) {
+            const int c = 16 * t + col;
+            if (t != wave) fetch(l, t, b, bias);
+#pragma unroll 1
+            for (int mb = 0; mb < MB; ++mb) {
+                const f32x4 acc = block_product(in + 16 * mb * kLd, b, ks, lane);
+                const int m = 16 * mb + mq;
+                bf16x4 h;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float v = acc[i] + bias;
+                    if (!last) {
+                        h[i] = c < fo ? (bf16)tanhf(v) : (bf16)0.0f;
+                    } else if (TRAIN) {
+                        const float d = (c < fo && m + i < rows) ? v - T[(r0 + m + i) * fo + c]
+                                                                 : 0.0f;
+                        h[i] = (bf16)(scale * d);
+                        e2 += d * d;
+                    } else if (c < fo && m + i < rows) {
+                        Y[(r0 + m + i) * fo + c] = v;
+                    }
+                }
+                if (last && !TRAIN) continue;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) out[(m + i) * kLd + c] = h[i];
+                if (TRAIN) put(last ? net.dT[l] : net.aT[l + 1], m, c, h);
+            }
+        }
+        if (!last || (TRAIN && net.L > 1)) fetch(l + 1, wave, b, bias);
+        __syncthreads();
+    }
+    if (!TRAIN) return;
+    // d_{l-1} = (d_l W_l^T) (1 - a_l^2), between the buffers past the activations
+    int cur = net.L;
+    for (int l = net.L - 1; l > 0; --l) {
+        const int fi = net.w[l], fo = net.w[l + 1], ks = (fo + 31) / 32;
+        const int step = 2 * net.L - 1 - l;
+        const bf16 *in = buf(cur), *a = buf(l);
+        cur = 2 * net.L + 1 - cur;
+        bf16 *out = buf(cur);
+        for (int t = wave; t < mlp_pad(fi) / 16; t += NW) {
+            const int c = 16 * t + col;
+            if (t != wave) fetch(step, t, b, bias);
+#pragma unroll 1
+            for (int mb = 0; mb < MB; ++mb) {
+                const f32x4 acc = block_product(in + 16 * mb * kLd, b, ks, lane);
+                const int m = 16 * mb + mq;
+                bf16x4 h;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float av = (float)a[(m + i) * kLd + c];
+                    h[i] = c < fi ? (bf16)(acc[i] * (1.0f - av * av)) : (bf16)0.0f;
+                    out[(m + i) * kLd + c] = h[i];
+                }
+                put(net.dT[l - 1], m, c, h);
+            }
+        }
+        if (l > 1) fetch(step + 1, wave, b, bias);
+        __syncthreads();
+    }
+    // the tile's sum of squared errors, in a fixed order
+    float *red = reinterpret_cast<float *>(sm);
+    red[threadIdx.x] = e2;
+    __syncthreads();
+    for (int s = 32 * NW; s > 0; s >>= 1) {
+        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) losspart[blockIdx.x] = red[0];
+}
+
+// All layers' weight gradients a_{l-1}^T d_l in one launch: wavefront (slice,
+// block) sums one 16 x 32 block over its slice of the rows into
+// part[slice][flat weight].  The workgroups past the blocks sum the bias
+// gradients of 16 columns of d_l each, in k_colsum's order: row r belongs to
+// partial sum r % 256, a thread holds eight consecutive ones of a column (one
+// 16-byte load a round) for two row groups, and the 256 are added as a tree.
+// 8,192 rows of the 6-128x4-4 network 14.4 us; one launch per layer and sum,
+// gathering both operands two bytes at a time, took 105.
+__global__ void __launch_bounds__(64 * kWaves)
+    k_mlp_wgrad(MlpNet net, int n, int kslice, int nblock, int items, float *__restrict__ part) {
+    const int gemm_wgs = (items + kWaves - 1) / kWaves;
+    const int lane = threadIdx.x & 63;
+    if ((int)blockIdx.x >= gemm_wgs) {
+        __shared__ float red[256][17];
+        int j = blockIdx.x - gemm_wgs, l = 0;
+        while (j >= (net.w[l + 1] + 15) / 16) j -= (net.w[++l] + 15) / 16;
+        const int steps = (n + 31) / 32;
+        const bf16 *d = net.dT[l] + (size_t)j * net.steps * kFrag;
+        // rows 8 g .. 8 g + 7 (mod 256) of column c; g and g + 16
+        const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
+        float s[2][8] = {};
+        auto add = [&](int st, float t[8]) {
+            const bf16x8 v = *reinterpret_cast<const bf16x8 *>(
+                d + (size_t)st * kFrag + ((g & 3) * 16 + c) * 8);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[i] += (float)v[i];
+        };
+        int k = g >> 2;  // whole rounds of 256 rows without a test, so that loads overlap
+#pragma unroll 8
+        for (; k + 8 - (g >> 2) <= steps; k += 8) {
+            add(k, s[0]);
+            add(k + 4, s[1]);
+        }
+        if (k < steps) add(k, s[0]);
+        if (k + 4 < steps) add(k + 4, s[1]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) red[128 * h + 8 * g + i][c] = s[h][i];
+        __syncthreads();
+        for (int h = 128; h > 0; h >>= 1) {
+            for (int r = g; r < h; r += 16) red[r][c] += red[r + h][c];
+            __syncthreads();
+        }
+        if (g == 0 && 16 * j + c < net.w[l + 1])
+            net.g[net.woff[l] + net.w[l] * net.w[l + 1] + 16 * j + c] = red[0][c];
+        return;
+    }
+    const int item = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (item >= items) return;  // whole wavefront leaves together
+    const int sl = item / nblock;
+    int blk = item - sl * nblock, l = 0, ntn;
+    for (;; ++l) {
+        const int ntm = (net.w[l] + 15) / 16;
+        ntn = (net.w[l + 1] + 31) / 32;
+        if (blk < ntm * ntn) break;
+        blk -= ntm * ntn;
+    }
+    const int fi = net.w[l], fo = net.w[l + 1];
+    const int i0 = blk / ntn, j0 = blk % ntn * 2;  // blocks of 16
+    const int kb = sl * kslice, ke = min(n, kb + kslice);
+    const bf16 *A = net.aT[l] + (size_t)i0 * net.steps * kFrag + 8 * lane;
+    const bf16 *B0 = net.dT[l] + (size_t)j0 * net.steps * kFrag + 8 * lane;
+    const bf16 *B1 = B0 + (size_t)net.steps * kFrag;
+    f32x4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll 4
+    for (int k = kb / 32; k < (ke + 31) / 32; ++k) {
+        const size_t o = (size_t)k * kFrag;
+        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(A + o);
+        const bf16x8 b0 = *reinterpret_cast<const bf16x8 *>(B0 + o);
+        const bf16x8 b1 = *reinterpret_cast<const bf16x8 *>(B1 + o);
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, acc[1], 0, 0, 0);
+    }
+    float *P = part + (size_t)sl * net.np + net.woff[l];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int j = 16 * (j0 + h) + (lane & 15);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 16 * i0 + 4 * (lane >> 4) + i;
+            if (r < fi && j < fo) P[(size_t)r * fo + j] = acc[h][i];
+        }
+    }
+}
+
+namespace {
+
+// bf16 copies of element (r, c) of W_l
+__device__ __forceinline__ void pack_weight(const MlpNet &net, int l, int r, int c, float w) {
+    const bf16 v = (bf16)w;
+    net.Wf[l][frag_index(c, r, (net.w[l] + 31) / 32)] = v;
+    net.Wr[l][frag_index(r, c, (net.w[l + 1] + 31) / 32)] = v;
+}
+
+__device__ __forceinline__ int layer_of(const MlpNet &net, int i) {
+    int l = 0;
+    while (l + 1 < net.L && i >= net.woff[l + 1]) ++l;
+    return l;
+}
+
+}  // namespace
+
+// every fragment element of layer blockIdx.y, the padding as zero
+__global__ void __launch_bounds__(256) k_mlp_pack(MlpNet net) {
+    const int l = blockIdx.y, fi = net.w[l], fo = net.w[l + 1];
+    const int i = blockIdx.x * 256 + threadIdx.x, r = i / mlp_pad(fo), c = i % mlp_pad(fo);
+    if (r >= mlp_pad(fi)) return;
+    pack_weight(net, l, r, c, (r < fi && c < fo) ? net.wt[net.woff[l] + r * fo + c] : 0.0f);
+}
+
+// Slices added in slice order into the gradient, one thread per parameter, and
+// with ADAM the step and the bf16 copies; the last workgroup adds the loss.
+template <bool ADAM>
+__global__ void __launch_bounds__(256)
+    k_mlp_update(MlpNet net, int nsl, const float *__restrict__ part, MlpAdam ad, int nloss,
+                 const float *__restrict__ losspart, float *__restrict__ loss) {
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ float red[256];
+        float s = 0.0f;
+        for (int i = threadIdx.x; i < nloss; i += 256) s += losspart[i];
+        red[threadIdx.x] = s;
+        __syncthreads();
+        for (int h = 128; h > 0; h >>= 1) {
+            if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) loss[0] = red[0];
+        return;
+    }
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= net.np) return;
+    const int l = layer_of(net, i), o = i - net.woff[l];
+    const bool weight = o < net.w[l] * net.w[l + 1];
+    float gi;
+    if (weight) {
+        gi = 0.0f;
+#pragma unroll 8
+        for (int sl = 0; sl < nsl; ++sl) gi += part[(size_t)sl * net.np + i];
+        net.g[i] = gi;
+    } else {
+        gi = net.g[i];
+    }
+    if (!ADAM) return;
+    const float w = adam_step(gi, ad.lr, ad.b1, ad.b2, ad.eps, ad.c1, ad.c2, net.wt + i, ad.m + i,
+                              ad.v + i);
+    if (weight) pack_weight(net, l, o / net.w[l + 1], o % net.w[l + 1], w);
+}
+
+bool mlp_fusable(const int *widths, int nwidth) {
+    if (nwidth - 1 > kFuseLayers) return false;
+    return std::all_of(widths, widths + nwidth, [](int w) { return w <= kFuseWidth; });
+}
+
+namespace {
+
+// slices of the weight gradients' inner dimension, as launch_mfma_gemm_splitk
+// takes them (no layer of a fusable network has more than kSplitKMaxTiles blocks)
+void batch_slices(int64_t n, int &nsl, int &kslice) {
+    nsl = gemm_splitk_slices(16, 16, (int)n);
+    kslice = nsl > 1 ? ((int)((n + nsl - 1) / nsl) + 31) / 32 * 32 : (int)n;
+    nsl = (int)((n + kslice - 1) / kslice);
+}
+
+size_t rows_lds(int mb, int bufs) { return (size_t)bufs * 16 * mb * kLd * sizeof(bf16); }
+
+}  // namespace
+
+// the slices asked for, which grow with n (those used need not: their length
+// is rounded to whole steps)
+size_t mlp_part_floats(int np, int64_t n) {
+    return (size_t)gemm_splitk_slices(16, 16, (int)n) * np;
+}
+
+// row tiles of a gradient of n rows: whole steps of 32 rows
+int64_t mlp_loss_parts(int64_t n) { return (n + 31) / 32 * 2; }
+
+// Tile and wavefronts by rows: tiles of 32 with four wavefronts read the weights
+// less often and keep more workgroups per CU than any other once the chip is
+// full (640,000 rows: 279 us; 16 rows 416, 32 rows with eight wavefronts 346, 64
+// rows 361 and 382); up to 32,768 rows tiles of 16 spread wider (20,000: 18.8
+// against 22.1 us), and up to 8,192, where a call is one chain of layers, a
+// wavefront per 16-column block shortens each (4,000: 8.0, with four
+// wavefronts 11.6, tiles of 32 18.2).
+hipError_t launch_mlp_forward(hipStream_t st, const MlpNet &net, const float *X, float *Y,
+                              int64_t n) {
+    if (n <= 0) return hipSuccess;
+    auto go = [&](auto kern, int mb, int nw) {
+        const int64_t wgs = (n + 16 * mb - 1) / (16 * mb);
+        hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * nw), rows_lds(mb, 2), st, net, n, X,
+                           (const float *)nullptr, Y, 0.0f, (float *)nullptr);
+        return hipGetLastError();
+    };
+    if (n <= 8192) return go(k_mlp_rows<1, 8, false>, 1, 8);
+    if (n <= 32768) return go(k_mlp_rows<1, 4, false>, 1, 4);
+    return go(k_mlp_rows<2, 4, false>, 2, 4);
+}
+
+// 16 rows per workgroup and a wavefront per 16-column block: the row kernel is
+// a chain of layers, and 8,192 rows then put two workgroups on each CU (23 us;
+// 32 rows and eight wavefronts 31, four 44).
+hipError_t launch_mlp_gradient(hipStream_t st, const MlpNet &net, const float *X, const float *T,
+                               int64_t n, float *part, float *losspart, float *loss,
+                               const MlpAdam *adam) {
+    const int nloss = (int)mlp_loss_parts(n);
+    const float scale = (float)(2.0 / (double)(n * net.w[net.L]));
+    hipLaunchKernelGGL((k_mlp_rows<1, 8, true>), dim3(nloss), dim3(64 * 8), rows_lds(1, net.L + 2),
+                       st, net, n, X, T, (float *)nullptr, scale, losspart);
+    int nsl, kslice, nblock = 0, cols = 0;
+    batch_slices(n, nsl, kslice);
+    for (int l = 0; l < net.L; ++l) {
+        nblock += ((net.w[l] + 15) / 16) * ((net.w[l + 1] + 31) / 32);
+        cols += (net.w[l + 1] + 15) / 16;
+    }
+    const int items = nblock * nsl;
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((items + kWaves - 1) / kWaves + cols), dim3(64 * kWaves), 0,
+                       st, net, (int)n, kslice, nblock, items, part);
+    const dim3 grid((net.np + 255) / 256 + 1), block(256);
+    if (adam)
+        hipLaunchKernelGGL(k_mlp_update<true>, grid, block, 0, st, net, nsl, part, *adam, nloss,
+                           losspart, loss);
+    else
+        hipLaunchKernelGGL(k_mlp_update<false>, grid, block, 0, st, net, nsl, part, MlpAdam{}, nloss,
+                           losspart, loss);
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_pack(hipStream_t st, const MlpNet &net) {
+    hipLaunchKernelGGL(k_mlp_pack, dim3(kFuseWidth * kFuseWidth / 256, net.L), dim3(256), 0, st, net);
     return hipGetLastError();
 }
 

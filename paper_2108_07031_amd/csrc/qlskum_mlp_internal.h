@@ -37,4 +37,46 @@ hipError_t launch_adam(hipStream_t st, int np, float lr, float b1, float b2, flo
 hipError_t launch_weights_bf16(hipStream_t st, int fi, int fo, const float *W, bf16 *Wb,
                                bf16 *WbT);
 
+// --- networks that fit the fused path ---------------------------------------
+// Every width at most kFuseWidth and at most kFuseLayers layers: a workgroup
+// then holds the activations of its rows in LDS through all layers.  Wider
+// layers would leave one workgroup per CU and are served by the products above.
+constexpr int kFuseWidth = 128, kFuseLayers = 6;
+
+// One network and its training workspace as the fused kernels see it.  The
+// matrix-core operands lie in memory as the instruction takes them, in
+// fragments of 16 columns by 32 steps of the inner dimension (frag_index), zero
+// in the padding: a wavefront reads a fragment as 1 KB in a row.
+struct MlpNet {
+    int L;                      // layers
+    int w[kFuseLayers + 1];     // widths
+    int woff[kFuseLayers];      // offset of W_l in the flat vectors (b_l follows)
+    int np;
+    bf16 *Wf[kFuseLayers], *Wr[kFuseLayers];  // W_l for a_{l-1} W_l and for d_l W_l^T
+    bf16 *aT[kFuseLayers], *dT[kFuseLayers];  // a_l and the error of layer l's output,
+    int steps;                  // whose inner dimension is the batch: room for 32 steps rows
+    float *wt, *g;              // FP32 weights and gradient (flat)
+};
+constexpr int mlp_pad(int w) { return (w + 31) & ~31; }
+bool mlp_fusable(const int *widths, int nwidth);
+// floats of workspace for the slices of a gradient of n rows or fewer
+size_t mlp_part_floats(int np, int64_t n);
+// loss partials of a gradient of n rows
+int64_t mlp_loss_parts(int64_t n);
+// Y = network(X), n rows
+hipError_t launch_mlp_forward(hipStream_t st, const MlpNet &net, const float *X, float *Y,
+                              int64_t n);
+// gradient of the mean squared error over n rows into net.g and the sum of
+// squared errors into *loss; with adam, one Adam step on net.wt, m and v and the
+// bf16 copies of the new weights
+struct MlpAdam {
+    float lr, b1, b2, eps, c1, c2;
+    float *m, *v;
+};
+hipError_t launch_mlp_gradient(hipStream_t st, const MlpNet &net, const float *X, const float *T,
+                               int64_t n, float *part, float *losspart, float *loss,
+                               const MlpAdam *adam);
+// the fragments of the FP32 weights net.wt
+hipError_t launch_mlp_pack(hipStream_t st, const MlpNet &net);
+
 }  // namespace ql

@@ -32,6 +32,11 @@ struct ql_mlp {
     bf16 *d[2] = {nullptr, nullptr};
     float *part = nullptr, *loss = nullptr;
     float *gpart = nullptr;  // split-K partial products of the weight gradients
+    // the fused kernels' view of a network they serve (act then holds the
+    // transposed activations, dT the transposed errors); net.L = 0: layer by
+    // layer with the buffers d and y
+    MlpNet net{};
+    std::vector<bf16 *> dT;
     int64_t t = 0;  // Adam steps taken
     bool has_weights = false;
 };
@@ -80,6 +85,10 @@ int ready(ql_mlp *m, bool need_weights) {
 
 // bf16 operand copies of every layer's weights
 int refresh_bf16(ql_mlp *m) {
+    if (m->net.L) {
+        MCHK(m, launch_mlp_pack(m->stream, m->net));
+        return QL_OK;
+    }
     for (int l = 0; l < nlayers(m); ++l)
         MCHK(m, launch_weights_bf16(m->stream, m->widths[l], m->widths[l + 1], m->w + m->woff[l],
                                     m->Wb[l], m->WbT[l]));
@@ -101,6 +110,13 @@ int forward(ql_mlp *m, const float *X, int64_t n) {
             MCHK(m, launch_mfma_gemm(m->stream, kEpiBias, true, true, (int)n, fo, fi, m->act[l],
                                      fi, m->WbT[l], fi, bias, nullptr, m->y, nullptr, fo));
     }
+    return QL_OK;
+}
+
+// forward + backward of one batch, and one Adam step if adam is given, with
+// three launches
+int fused_gradient(ql_mlp *m, const float *X, const float *T, int64_t n, const MlpAdam *adam) {
+    MCHK(m, launch_mlp_gradient(m->stream, m->net, X, T, n, m->gpart, m->part, m->loss, adam));
     return QL_OK;
 }
 
@@ -132,6 +148,68 @@ int gradient(ql_mlp *m, const float *X, const float *T, int64_t n) {
         }
     }
     return QL_OK;
+}
+
+// Buffers of the fused path; false (and none kept) if they do not fit, as a
+// network close to the device's memory then runs layer by layer in less.
+bool alloc_fused(ql_mlp *m) {
+    const int L = nlayers(m);
+    const size_t rows = ((size_t)m->max_batch + 31) / 32 * 32;
+    m->dT.assign(L, nullptr);
+    bool ok = malloc_n(&m->gpart, mlp_part_floats(m->np, m->max_batch)) == hipSuccess &&
+              malloc_n(&m->part, (size_t)mlp_loss_parts(m->max_batch)) == hipSuccess;
+    for (int l = 0; ok && l < L; ++l) {
+        const int fi = mlp_pad(m->widths[l]), fo = mlp_pad(m->widths[l + 1]);
+        const size_t nw = (size_t)fi * fo;
+        ok = malloc_n(&m->act[l], rows * fi) == hipSuccess &&
+             malloc_n(&m->dT[l], rows * fo) == hipSuccess &&
+             malloc_n(&m->Wb[l], nw) == hipSuccess && malloc_n(&m->WbT[l], nw) == hipSuccess;
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        for (auto *v : {&m->act, &m->dT, &m->Wb, &m->WbT})
+            for (auto &p : *v) free_p(p);
+        free_p(m->gpart);
+        free_p(m->part);
+        return false;
+    }
+    MlpNet &t = m->net;
+    t.L = L;
+    for (int l = 0; l <= L; ++l) t.w[l] = m->widths[l];
+    for (int l = 0; l < L; ++l) {
+        t.woff[l] = m->woff[l];
+        t.Wf[l] = m->WbT[l];
+        t.Wr[l] = m->Wb[l];
+        t.aT[l] = m->act[l];
+        t.dT[l] = m->dT[l];
+    }
+    t.np = m->np;
+    t.steps = (int)(rows / 32);
+    t.wt = m->w;
+    t.g = m->g;
+    return true;
+}
+
+// Buffers of the layer-by-layer path.
+bool alloc_layers(ql_mlp *m, int maxw) {
+    const int L = nlayers(m);
+    bool ok = true;
+    for (int l = 0; ok && l < L; ++l) {
+        const size_t nw = (size_t)m->widths[l] * m->widths[l + 1];
+        ok = malloc_n(&m->Wb[l], nw) == hipSuccess && malloc_n(&m->WbT[l], nw) == hipSuccess &&
+             malloc_n(&m->act[l], (size_t)m->max_batch * m->widths[l]) == hipSuccess;
+    }
+    const int64_t cnt = m->max_batch * m->widths[L];
+    ok = ok && malloc_n(&m->y, (size_t)cnt) == hipSuccess &&
+         malloc_n(&m->d[0], (size_t)m->max_batch * maxw) == hipSuccess &&
+         malloc_n(&m->d[1], (size_t)m->max_batch * maxw) == hipSuccess &&
+         malloc_n(&m->part, (size_t)((cnt + 255) / 256)) == hipSuccess;
+    size_t gp = 0;
+    for (int l = 0; l < L; ++l) {
+        const int nsl = gemm_splitk_slices(m->widths[l], m->widths[l + 1], (int)m->max_batch);
+        if (nsl > 1) gp = std::max(gp, (size_t)nsl * m->widths[l] * m->widths[l + 1]);
+    }
+    return ok && (gp == 0 || malloc_n(&m->gpart, gp) == hipSuccess);
 }
 
 int check_batch(ql_mlp *m, const void *X, const void *T, int64_t n, bool need_t) {
@@ -184,23 +262,9 @@ int ql_mlp_create(ql_mlp **out, int32_t device, void *hip_stream, const int32_t 
     m->Wb.assign(nwidth - 1, nullptr);
     m->WbT.assign(nwidth - 1, nullptr);
     m->act.assign(nwidth - 1, nullptr);
-    for (int l = 0; okm && l + 1 < nwidth; ++l) {
-        okm = malloc_n(&m->Wb[l], (size_t)widths[l] * widths[l + 1]) == hipSuccess &&
-              malloc_n(&m->WbT[l], (size_t)widths[l] * widths[l + 1]) == hipSuccess &&
-              malloc_n(&m->act[l], (size_t)max_batch * widths[l]) == hipSuccess;
-    }
-    const int64_t cnt = max_batch * widths[nwidth - 1];
-    okm = okm && malloc_n(&m->y, (size_t)cnt) == hipSuccess &&
-          malloc_n(&m->d[0], (size_t)max_batch * maxw) == hipSuccess &&
-          malloc_n(&m->d[1], (size_t)max_batch * maxw) == hipSuccess &&
-          malloc_n(&m->part, (size_t)((cnt + 255) / 256)) == hipSuccess &&
-          malloc_n(&m->loss, 1) == hipSuccess;
-    size_t gp = 0;
-    for (int l = 0; l + 1 < nwidth; ++l) {
-        const int nsl = gemm_splitk_slices(widths[l], widths[l + 1], (int)max_batch);
-        if (nsl > 1) gp = std::max(gp, (size_t)nsl * widths[l] * widths[l + 1]);
-    }
-    okm = okm && (gp == 0 || malloc_n(&m->gpart, gp) == hipSuccess);
+    okm = okm && malloc_n(&m->loss, 1) == hipSuccess;
+    if (okm && !(mlp_fusable(m->widths.data(), nwidth) && alloc_fused(m)))
+        okm = alloc_layers(m, maxw);
     if (!okm) {
         ql_mlp_destroy(m);
         return QL_ENOMEM;
@@ -217,6 +281,7 @@ int ql_mlp_destroy(ql_mlp *m) {
     for (auto &p : m->Wb) free_p(p);
     for (auto &p : m->WbT) free_p(p);
     for (auto &p : m->act) free_p(p);
+    for (auto &p : m->dT) free_p(p);
     free_p(m->y); free_p(m->d[0]); free_p(m->d[1]); free_p(m->part); free_p(m->loss);
     free_p(m->gpart);
     if (m->own_stream && m->stream) (void)hipStreamDestroy(m->stream);
@@ -263,6 +328,10 @@ int ql_mlp_forward(ql_mlp *m, const float *X, float *Y, int64_t n) {
     if (st) return st;
     if (n < 0 || (n > 0 && (!X || !Y))) return mfail(m, QL_EINVAL, "bad forward arguments");
     const int w0 = m->widths.front(), wL = m->widths.back();
+    if (m->net.L) {
+        MCHK(m, launch_mlp_forward(m->stream, m->net, X, Y, n));
+        return QL_OK;
+    }
     for (int64_t r = 0; r < n; r += m->max_batch) {
         const int64_t b = std::min(m->max_batch, n - r);
         if ((st = forward(m, X + r * w0, b))) return st;
@@ -277,7 +346,7 @@ int ql_mlp_gradient(ql_mlp *m, const float *X, const float *T, int64_t n, float 
     int st = ready(m, true);
     if (st) return st;
     if ((st = check_batch(m, X, T, n, true))) return st;
-    if ((st = gradient(m, X, T, n))) return st;
+    if ((st = m->net.L ? fused_gradient(m, X, T, n, nullptr) : gradient(m, X, T, n))) return st;
     float l = 0.0f;
     if (grad)
         MCHK(m, hipMemcpyAsync(grad, m->g, sizeof(float) * m->np, hipMemcpyDeviceToHost,
@@ -294,14 +363,19 @@ int ql_mlp_train_step(ql_mlp *m, const float *X, const float *T, int64_t n, floa
     if (st) return st;
     if ((st = check_batch(m, X, T, n, true))) return st;
     if (!(lr > 0.0f) || !std::isfinite(lr)) return mfail(m, QL_EINVAL, "bad learning rate");
-    if ((st = gradient(m, X, T, n))) return st;
+    if (!m->net.L && (st = gradient(m, X, T, n))) return st;
     m->t += 1;
     const double b1 = 0.9, b2 = 0.999;
     const float c1 = (float)(1.0 / (1.0 - std::pow(b1, (double)m->t)));
     const float c2 = (float)(1.0 / (1.0 - std::pow(b2, (double)m->t)));
-    MCHK(m, launch_adam(m->stream, m->np, lr, (float)b1, (float)b2, 1e-8f, c1, c2, m->g, m->w,
-                        m->m, m->v));
-    if ((st = refresh_bf16(m))) return st;
+    if (m->net.L) {
+        const MlpAdam ad{lr, (float)b1, (float)b2, 1e-8f, c1, c2, m->m, m->v};
+        if ((st = fused_gradient(m, X, T, n, &ad))) return st;
+    } else {
+        MCHK(m, launch_adam(m->stream, m->np, lr, (float)b1, (float)b2, 1e-8f, c1, c2, m->g, m->w,
+                            m->m, m->v));
+        if ((st = refresh_bf16(m))) return st;
+    }
     if (loss) {
         float l = 0.0f;
         MCHK(m, hipMemcpyAsync(&l, m->loss, sizeof(float), hipMemcpyDeviceToHost, m->stream));
