@@ -1330,10 +1330,10 @@ __device__ __forceinline__ double wave_sum(double v) {
 // Written with explicit fma and no implicit contraction: a point's residual
 // depends only on its data and on the order of its entries, never on the code
 // path that gathered them.  Returns false when a modified state has no
-// Maxwellian.  FIRST: first-order scheme, the split fluxes of q itself.
+// Maxwellian.
 // M: the split stencils evaluated (Split bits; 15 all four).  The caller
 // masks f with M, so a direction is evaluated when M holds either half.
-template <bool LIMITER, int POW, bool FIRST, int M = 15>
+template <bool LIMITER, int POW, int M = 15>
 __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, double2 N,
                                            const double qi[4], const double gi[8],
                                            const double bi[8], const double qp[4],
@@ -1345,13 +1345,7 @@ __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, doub
     const double ds = fma(dx, tx, dy * ty);
     const double dn = fma(dx, N.x, dy * N.y);
     double qti[4], qt0[4];
-    if (FIRST) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            qti[r] = qi[r];
-            qt0[r] = qp[r];
-        }
-    } else if (LIMITER) {
+    if (LIMITER) {
         const double e = fp.venkat_k * fast_sqrt(fma(dx, dx, dy * dy));
         const double eps2 = fmax((e * e) * e, kEps2Min);
         // -1/2 folded into the offsets: scaling by a power of two commutes
@@ -1431,7 +1425,7 @@ __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, doub
 // p's own modified state is shifted by the mirrored offset as in eq. (28).
 // Adds w (G_inf - Gn-(q~_p)) with w the mirrored stencil's n-derivative
 // weight (k_setup stores the mirrored factors in p's n- slot).
-template <bool LIMITER, int POW, bool FIRST>
+template <bool LIMITER, int POW>
 __device__ __forceinline__ bool mirror_entry(double dx, double dy, double2 N, const double qp[4],
                                              const double gp[8], const double bp[8],
                                              const double w[8], const double Ginf[4],
@@ -1442,10 +1436,7 @@ __device__ __forceinline__ bool mirror_entry(double dx, double dy, double2 N, co
     const double dm = -fma(dx, N.x, dy * N.y);
     const double mx = fma(ds, tx, dm * N.x), my = fma(ds, ty, dm * N.y);
     double qt0[4];
-    if (FIRST) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) qt0[r] = qp[r];
-    } else if (LIMITER) {
+    if (LIMITER) {
         const double e = fp.venkat_k * fast_sqrt(fma(mx, mx, my * my));
         const double eps2 = fmax((e * e) * e, kEps2Min);
         const double hx = -0.5 * mx, hy = -0.5 * my;
@@ -1618,11 +1609,11 @@ struct OwnPoint {
 // staging waits for two memory round trips whatever the image holds (a loop
 // over single parts waited for two per part: with OwnPoint's early loads,
 // k_flux on a 632k-point cloud with the limiter 337 -> 305 us).
-template <bool LIMITER, bool FIRST>
+template <bool LIMITER>
 __device__ __forceinline__ void stage_records(const DevCloud &cl, double2 *lds, int base, int nown,
                                               int h0, int ns, const double2 *q, const double2 *g,
                                               const double2 *qmm) {
-    constexpr int kRec = FIRST ? 3 : (LIMITER ? 11 : 7);
+    constexpr int kRec = LIMITER ? 11 : 7;
     constexpr int kIt = 5;  // slots per lane in flight; 320 slots cover the default budget
     const int c = threadIdx.x & 3;
     for (int s0 = threadIdx.x >> 2; s0 < ns; s0 += kIt * (kBlock / 4)) {
@@ -1639,7 +1630,7 @@ __device__ __forceinline__ void stage_records(const DevCloud &cl, double2 *lds, 
         for (int i = 0; i < kIt; ++i) {
             const size_t p = max(pt[i], 0);  // in range where the slot is unused
             a[i] = *(c < 2 ? q + 2 * p + c : cl.xy + p);
-            if (!FIRST) d[i] = g[4 * p + c];
+            d[i] = g[4 * p + c];
             if (LIMITER) b[i] = qmm[4 * p + c];
         }
 #pragma unroll
@@ -1647,7 +1638,7 @@ __device__ __forceinline__ void stage_records(const DevCloud &cl, double2 *lds, 
             if (pt[i] < 0) continue;
             double2 *r = lds + kRec * (s0 + i * (kBlock / 4));
             if (c < 3) r[c < 2 ? c : kRec - 1] = a[i];
-            if (!FIRST) r[2 + c] = d[i];
+            r[2 + c] = d[i];
             if (LIMITER) r[6 + c] = b[i];
         }
     }
@@ -1657,18 +1648,18 @@ __device__ __forceinline__ void stage_records(const DevCloud &cl, double2 *lds, 
 // o.k, o.k + kFluxLanes, ...; IN_LDS: the records come from the tile's LDS
 // image, else from memory (one instantiation each, so that no load is
 // generic).  Reports a failed reconstruction.
-template <bool IN_LDS, bool LIMITER, int POW, bool FIRST, int M, bool KOBC>
+template <bool IN_LDS, bool LIMITER, int POW, int M, bool KOBC>
 __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams &fp,
                                            const double2 *lds, int j, int p, const OwnPoint &o,
                                            const double2 *q, const double2 *g,
                                            const double2 *qmm, double R[4], ErrWord *err) {
-    constexpr int kRec = FIRST ? 3 : (LIMITER ? 11 : 7);
+    constexpr int kRec = LIMITER ? 11 : 7;
     double qp[4], gp[8], bp[8];
     if constexpr (IN_LDS) {
         const double2 *r = lds + kRec * j;
         qp[0] = r[0].x; qp[1] = r[0].y; qp[2] = r[1].x; qp[3] = r[1].y;
 #pragma unroll
-        for (int m = 0; m < 4 && !FIRST; ++m) {
+        for (int m = 0; m < 4; ++m) {
             gp[2 * m] = r[2 + m].x;
             gp[2 * m + 1] = r[2 + m].y;
             if (LIMITER) {
@@ -1678,7 +1669,7 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
         }
     } else {
         load4(q, p, qp);
-        if (!FIRST) load8(g, p, gp);
+        load8(g, p, gp);
         if (LIMITER) load8(qmm, p, bp);
     }
     // walls drop n+ (its stencil lies in the body), outer points n- (it
@@ -1710,7 +1701,7 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
             const double2 *r = lds + kRec * i;
             qi[0] = r[0].x; qi[1] = r[0].y; qi[2] = r[1].x; qi[3] = r[1].y;
 #pragma unroll
-            for (int m = 0; m < 4 && !FIRST; ++m) {
+            for (int m = 0; m < 4; ++m) {
                 gi[2 * m] = r[2 + m].x;
                 gi[2 * m + 1] = r[2 + m].y;
                 if (LIMITER) {
@@ -1721,11 +1712,11 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
             Q = r[kRec - 1];
         } else {
             load4(q, i, qi);
-            if (!FIRST) load8(g, i, gi);
+            load8(g, i, gi);
             if (LIMITER) load8(qmm, i, bi);
             Q = cl.xy[i];
         }
-        ok &= flux_entry<LIMITER, POW, FIRST, M>(f, Q.x - o.P.x, Q.y - o.P.y, o.N, qi, gi, bi, qp,
+        ok &= flux_entry<LIMITER, POW, M>(f, Q.x - o.P.x, Q.y - o.P.y, o.N, qi, gi, bi, qp,
                                                  gp, bp, o.w, fp, R);
     }
     if constexpr (KOBC && (M & kNMinus)) {
@@ -1736,7 +1727,7 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
                 if (!(cl.flag[k] & kNPlus)) continue;
                 const double2 Q = IN_LDS ? lds[kRec * (int)cl.flidx[k] + kRec - 1]
                                          : cl.xy[cl.idx[k]];
-                ok &= mirror_entry<LIMITER, POW, FIRST>(Q.x - o.P.x, Q.y - o.P.y, o.N, qp, gp, bp,
+                ok &= mirror_entry<LIMITER, POW>(Q.x - o.P.x, Q.y - o.P.y, o.N, qp, gp, bp,
                                                         o.w, Ginf, fp, R);
             }
         }
@@ -1746,7 +1737,7 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
 
 }  // namespace
 
-template <bool LIMITER, int POW, bool FIRST, int M, bool KOBC>
+template <bool LIMITER, int POW, int M, bool KOBC>
 // Held to 3 waves per SIMD (at most 168 VGPRs), which the straight-line
 // two-direction body of flux_entry would otherwise exceed.
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
@@ -1761,7 +1752,6 @@ k_flux(DevCloud cl, FlowParams fp, int stage, int cap,
                                                  double *__restrict__ Rout,
                                                  float4 *__restrict__ q32next, ErrWord *err) {
     // slot record (double2): q 0..1, g 2..5, bound offsets 6..9, position last
-    // (first order: q and position only)
     extern __shared__ double2 lds[];
     const int n = cl.n;
     const int t = sweep_tile(cl);
@@ -1779,7 +1769,7 @@ k_flux(DevCloud cl, FlowParams fp, int stage, int cap,
     const int p = base + j;
     OwnPoint o;
     if (j < nown) o.load(cl, p, sub);
-    if (in_lds) stage_records<LIMITER, FIRST>(cl, lds, base, nown, h0, ns, q, g, qmm);
+    if (in_lds) stage_records<LIMITER>(cl, lds, base, nown, h0, ns, q, g, qmm);
     __syncthreads();
     double R[4] = {0.0, 0.0, 0.0, 0.0};
     uint8_t kd = kOuter;
@@ -1797,9 +1787,9 @@ k_flux(DevCloud cl, FlowParams fp, int stage, int cap,
     const double2 N = o.N;
     if (live) {
         if (in_lds)
-            flux_point<true, LIMITER, POW, FIRST, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R, err);
+            flux_point<true, LIMITER, POW, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R, err);
         else
-            flux_point<false, LIMITER, POW, FIRST, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R,
+            flux_point<false, LIMITER, POW, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R,
                                                             err);
     }
     double Rs = lane_group_sum4(R, sub);
@@ -1807,6 +1797,179 @@ k_flux(DevCloud cl, FlowParams fp, int stage, int cap,
     // the other directions' part (split launches)
     if (Rin && live) Rs += Rin[(size_t)sub * n + p];
     finish_point(cl, fp, stage, p, sub, live, kd, N, Rs, q, U, Un, dt, qnext, Rout, q32next, err);
+}
+
+// ---------------------------------------------------------------------------
+// First-order flux residual + Runge-Kutta stage (FP64).  The split fluxes are
+// those of q itself, so nothing but the direction and the sign of a flux depends
+// on the entry: the primitive state is formed once per staged point (2.9 per
+// point of a tile, 2 per entry before), and the point's own four split fluxes
+// once, one per lane, into LDS.  An entry is left with two split fluxes instead
+// of two conversions and four: 144k points 48.0 -> 37.8 us, 632k 178 -> 136
+// (issue bound; five waves per SIMD instead of four spill: 153).  The operations, and
+// so the results, are those of the entry-by-entry form.
+// Slot record (double2): (rho, u1), (u2, p), (sqrt(beta), bk), (h, k), position;
+// p is NaN where the state has no Maxwellian.
+// ---------------------------------------------------------------------------
+namespace {
+
+template <int POW>
+__device__ __forceinline__ Prim first_order_prim(const double2 *q, int i, const FlowParams &fp) {
+    double qv[4];
+    load4(q, i, qv);
+    Prim s;
+    if (!q_to_prim<POW>(qv, fp, s)) s.p = NAN;
+    return s;
+}
+
+constexpr int kFirstRec = 5;
+
+// the lane's entries, IN_LDS as in flux_point; G0 holds the point's own split
+// fluxes G_s+, G_s-, G_n+, G_n-
+template <bool IN_LDS, int POW, bool KOBC>
+__device__ __forceinline__ bool first_order_point(const DevCloud &cl, const FlowParams &fp,
+                                                  const double2 *lds, const double2 *G0, int p,
+                                                  const OwnPoint &o, const double2 *q,
+                                                  double R[4]) {
+#pragma clang fp contract(off)
+    const double tx = o.N.y, ty = -o.N.x;
+    uint8_t fmask = (o.kd == kWall) ? uint8_t(~kNPlus) : uint8_t(0xff);
+    if constexpr (KOBC) {
+        if (o.kd == kOuter) fmask &= uint8_t(~kNMinus);
+    }
+    bool ok = true;
+    for (int k = o.k; k < o.k1; k += kFluxLanes) {
+        const uint8_t f = cl.flag[k] & fmask;
+        if (f == 0) continue;
+        Prim s;
+        double2 Q;
+        if constexpr (IN_LDS) {
+            const double2 *r = lds + kFirstRec * (int)cl.flidx[k];
+            s.rho = r[0].x; s.u1 = r[0].y; s.u2 = r[1].x; s.p = r[1].y;
+            s.sqb = r[2].x; s.bk = r[2].y; s.h = r[3].x; s.k = r[3].y;
+            Q = r[4];
+        } else {
+            const int i = cl.idx[k];
+            s = first_order_prim<POW>(q, i, fp);
+            Q = cl.xy[i];
+        }
+        ok &= isfinite(s.p);
+        const double dx = Q.x - o.P.x, dy = Q.y - o.P.y;
+        const double ds = fma(dx, tx, dy * ty);
+        const double dn = fma(dx, o.N.x, dy * o.N.y);
+        const bool sp = (f & kSPlus) != 0, np = (f & kNPlus) != 0;
+        const double sgs = sp ? 1.0 : -1.0, sgn = np ? 1.0 : -1.0;
+        HalfRange hs, hn;
+        hs.near(s, tx, ty, sgs);
+        hn.near(s, o.N.x, o.N.y, sgn);
+        if (fmax(fabs(hs.S), fabs(hn.S)) > kErfNear64) {
+            hs.far(sgs);
+            hn.far(sgn);
+        }
+        const double ws = (f & (kSPlus | kSMinus))
+                              ? fma(ds, sp ? o.w[0] : o.w[2], -(dn * (sp ? o.w[1] : o.w[3]))) : 0.0;
+        const double wn = (f & (kNPlus | kNMinus))
+                              ? fma(dn, np ? o.w[4] : o.w[6], -(ds * (np ? o.w[5] : o.w[7]))) : 0.0;
+        double G[4];
+        split_flux(s, hs, tx, ty, sgs, G);
+        const double2 *g = G0 + (sp ? 0 : 2);
+        const double2 a0 = g[0], a1 = g[1];
+        R[0] = fma(ws, G[0] - a0.x, R[0]);
+        R[1] = fma(ws, G[1] - a0.y, R[1]);
+        R[2] = fma(ws, G[2] - a1.x, R[2]);
+        R[3] = fma(ws, G[3] - a1.y, R[3]);
+        split_flux(s, hn, o.N.x, o.N.y, sgn, G);
+        g = G0 + (np ? 4 : 6);
+        const double2 b0 = g[0], b1 = g[1];
+        R[0] = fma(wn, G[0] - b0.x, R[0]);
+        R[1] = fma(wn, G[1] - b0.y, R[1]);
+        R[2] = fma(wn, G[2] - b1.x, R[2]);
+        R[3] = fma(wn, G[3] - b1.y, R[3]);
+    }
+    if constexpr (KOBC) {
+        if (o.kd == kOuter) {  // the mirrored n- stencil of mirror_entry
+            double Ginf[4];
+            ok &= freestream_flux<POW>(cl.uinf + 4 * cl.case_of[p], o.N, fp, Ginf);
+            const double2 b0 = G0[6], b1 = G0[7];
+            for (int k = o.k; k < o.k1; k += kFluxLanes) {
+                if (!(cl.flag[k] & kNPlus)) continue;
+                const double2 Q = IN_LDS ? lds[kFirstRec * (int)cl.flidx[k] + 4]
+                                         : cl.xy[cl.idx[k]];
+                const double dx = Q.x - o.P.x, dy = Q.y - o.P.y;
+                const double ds = fma(dx, tx, dy * ty);
+                const double dm = -fma(dx, o.N.x, dy * o.N.y);
+                const double wm = fma(dm, o.w[6], -(ds * o.w[7]));
+                R[0] = fma(wm, Ginf[0] - b0.x, R[0]);
+                R[1] = fma(wm, Ginf[1] - b0.y, R[1]);
+                R[2] = fma(wm, Ginf[2] - b1.x, R[2]);
+                R[3] = fma(wm, Ginf[3] - b1.y, R[3]);
+            }
+        }
+    }
+    return ok;
+}
+
+}  // namespace
+
+template <int POW, bool KOBC>
+__global__ void __launch_bounds__(kBlock)
+k_flux_first(DevCloud cl, FlowParams fp, int stage, int cap, const double2 *__restrict__ q,
+             double *__restrict__ U, double *__restrict__ Un, double *__restrict__ dt,
+             double2 *__restrict__ qnext, double *__restrict__ Rout, float4 *__restrict__ q32next,
+             ErrWord *err) {
+    extern __shared__ double2 lds[];
+    __shared__ double2 G0[kFluxTile][8];
+    const int t = sweep_tile(cl);
+    if (cl.tile_active && !cl.tile_active[t]) return;
+    if (cl.tile_prec && cl.tile_prec[t] != 0) return;  // an FP32-flux tile
+    const TileInfo ti = tile_info(cl, t, cap);
+    const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
+    const int p = ti.base + j;
+    const bool own = j < ti.nown;
+    OwnPoint o;
+    if (own) o.load(cl, p, sub);
+    if (ti.in_lds) {
+        for (int s0 = threadIdx.x; s0 < ti.ns; s0 += kBlock) {
+            const int i = slot_point(cl, ti, s0);
+            if (i < 0) continue;
+            const double2 Q = cl.xy[i];
+            const Prim s = first_order_prim<POW>(q, i, fp);
+            double2 *r = lds + kFirstRec * s0;
+            r[0] = make_double2(s.rho, s.u1);
+            r[1] = make_double2(s.u2, s.p);
+            r[2] = make_double2(s.sqb, s.bk);
+            r[3] = make_double2(s.h, s.k);
+            r[4] = Q;
+        }
+    }
+    bool ok0 = true;
+    if (own) {
+        // lane 0: s+, 1: s-, 2: n+, 3: n-
+        const Prim s = first_order_prim<POW>(q, p, fp);
+        ok0 = isfinite(s.p);
+        const bool n = sub >= 2;
+        double G[4];
+        split_flux(s, n ? o.N.x : o.N.y, n ? o.N.y : -o.N.x, (sub & 1) ? -1.0 : 1.0, G);
+        G0[j][2 * sub] = make_double2(G[0], G[1]);
+        G0[j][2 * sub + 1] = make_double2(G[2], G[3]);
+    }
+    __syncthreads();
+    double R[4] = {0.0, 0.0, 0.0, 0.0};
+    bool live = false;
+    if (own) {
+        const bool frozen = cl.case_active && !cl.case_active[cl.case_of[p]];
+        live = (KOBC || o.kd != kOuter) && !frozen;
+    }
+    if (live) {
+        const bool ok = ti.in_lds
+                            ? first_order_point<true, POW, KOBC>(cl, fp, lds, G0[j], p, o, q, R)
+                            : first_order_point<false, POW, KOBC>(cl, fp, lds, G0[j], p, o, q, R);
+        if (!(ok && ok0)) report_pt(cl, err, p, kErrPositivity);
+    }
+    const double Rs = lane_group_sum4(R, sub);
+    if (!own) return;
+    finish_point(cl, fp, stage, p, sub, live, o.kd, o.N, Rs, q, U, Un, dt, qnext, Rout, q32next,
+                 err);
 }
 
 namespace {
@@ -1839,7 +2002,7 @@ hipError_t launch_flux(hipStream_t st, const DevCloud &c, const FlowParams &fp, 
                        double *U, double *Un, double *dt, double2 *qnext, double *Rout,
                        float4 *q32next, ErrWord *err, int split, double *const Rpart[2]) {
     const bool first = fp.order == 1;
-    const int rec = (first ? 3 : fp.limiter ? 11 : 7) * (int)sizeof(double2);
+    const int rec = (first ? kFirstRec : fp.limiter ? 11 : 7) * (int)sizeof(double2);
     const int cap = lds_cap(c, lds_budget, rec);
     const size_t shmem = (size_t)cap * rec;
     const dim3 grid(sweep_grid(c)), block(kBlock);
@@ -1847,13 +2010,17 @@ hipError_t launch_flux(hipStream_t st, const DevCloud &c, const FlowParams &fp, 
         hipLaunchKernelGGL(kern, grid, block, shmem, st, c, fp, stg, cap, rin, q, g, qmm, U, Un,
                            dt, qnext, rout, q32next, err);
     };
-    if (first) {  // first order: one fused launch
+    if (first) {  // one fused launch
+        auto go1 = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, block, shmem, st, c, fp, stage, cap, q, U, Un, dt, qnext,
+                               Rout, q32next, err);
+        };
         if (fp.sqrt_pow == 5) {
-            if (fp.kobc) go(k_flux<false, 5, true, 15, true>, stage, nullptr, Rout);
-            else go(k_flux<false, 5, true, 15, false>, stage, nullptr, Rout);
+            if (fp.kobc) go1(k_flux_first<5, true>);
+            else go1(k_flux_first<5, false>);
         } else {
-            if (fp.kobc) go(k_flux<false, 0, true, 15, true>, stage, nullptr, Rout);
-            else go(k_flux<false, 0, true, 15, false>, stage, nullptr, Rout);
+            if (fp.kobc) go1(k_flux_first<0, true>);
+            else go1(k_flux_first<0, false>);
         }
         return hipGetLastError();
     }
@@ -1862,16 +2029,16 @@ hipError_t launch_flux(hipStream_t st, const DevCloud &c, const FlowParams &fp, 
         constexpr int P = decltype(pw)::value;
         if (split == 2) {
             // the s directions, then the n directions with the update
-            go(k_flux<L, P, false, kSPlus | kSMinus, false>, 0, nullptr, Rpart[0]);
-            go(k_flux<L, P, false, kNPlus | kNMinus, K>, stage, Rpart[0], Rout);
+            go(k_flux<L, P, kSPlus | kSMinus, false>, 0, nullptr, Rpart[0]);
+            go(k_flux<L, P, kNPlus | kNMinus, K>, stage, Rpart[0], Rout);
         } else if (split == 4) {
             // one launch per split stencil, the last with the update
-            go(k_flux<L, P, false, kSPlus, false>, 0, nullptr, Rpart[0]);
-            go(k_flux<L, P, false, kSMinus, false>, 0, Rpart[0], Rpart[1]);
-            go(k_flux<L, P, false, kNPlus, false>, 0, Rpart[1], Rpart[0]);
-            go(k_flux<L, P, false, kNMinus, K>, stage, Rpart[0], Rout);
+            go(k_flux<L, P, kSPlus, false>, 0, nullptr, Rpart[0]);
+            go(k_flux<L, P, kSMinus, false>, 0, Rpart[0], Rpart[1]);
+            go(k_flux<L, P, kNPlus, false>, 0, Rpart[1], Rpart[0]);
+            go(k_flux<L, P, kNMinus, K>, stage, Rpart[0], Rout);
         } else {
-            go(k_flux<L, P, false, 15, K>, stage, nullptr, Rout);
+            go(k_flux<L, P, 15, K>, stage, nullptr, Rout);
         }
     });
     return hipGetLastError();

@@ -42,3 +42,27 @@ def test_flux_across_the_near_line(ql, mach, limiter, order):
     err, floor = normwise_rel(R, ref), normwise_rel(fma, ref)
     print("  error", err, "floor", floor, flush=True)
     assert err.max() <= 10.0 * floor.max()
+
+
+@pytest.mark.parametrize("outer_bc", [0, 1])
+@pytest.mark.parametrize("gamma", [1.4, 1.3])
+def test_first_order_records(ql, gamma, outer_bc):
+    """First order: primitive states staged once per point against states
+    converted at every entry from memory (flux_lds 16), and a budget between
+    them that stages some tiles only, bit for bit, over a cloud that ends
+    inside a tile and holds states past the line above."""
+    print(f"first order gamma={gamma} outer_bc={outer_bc}", flush=True)
+    c = cloud("small") if outer_bc else cloud("jitter")
+    U = smooth_state(c, mach=1.49, alpha_deg=2.0, amp=0.05, gamma=gamma)
+    out = []
+    for b in (0, 16, 160 * 80):
+        s = ql.Solver(c, mach=1.49, alpha_deg=2.0, order=1, gamma=gamma, outer_bc=outer_bc,
+                      flux_lds=b)
+        s.set_state(U)
+        R = s.evaluate()["R"]
+        s.set_state(U)
+        out.append((R, s.step(5), s.fetch_state()))
+        s.close()
+    for o in out[1:]:
+        for a, b in zip(o, out[0]):
+            np.testing.assert_array_equal(a, b)
