@@ -597,6 +597,22 @@ __device__ __forceinline__ int slot_point(const DevCloud &cl, const TileInfo &ti
 
 }  // namespace
 
+// entry slots a q-derivative workgroup stages in LDS (tiles with more entries
+// read them from memory)
+constexpr int kCapE = 2048;
+
+// The tile's entry slots flidx[e0 .. e0 + ne), copied into LDS in 16-byte
+// chunks from the chunk that holds e0 (one load per lane for a tile of 64
+// 24-entry points, where single slots took six dependent rounds); entry k is
+// then at eidx[k - e0a].  The array is padded to a whole chunk.
+__device__ __forceinline__ int entry_origin(int e0) { return e0 & ~7; }
+__device__ __forceinline__ void stage_entries(const DevCloud &cl, uint16_t *eidx, int e0, int ne) {
+    const int e0a = entry_origin(e0), nc = (e0 + ne - e0a + 7) / 8;
+    const uint4 *src = reinterpret_cast<const uint4 *>(cl.flidx + e0a);
+    for (int c = threadIdx.x; c < nc; c += kBlock) reinterpret_cast<uint4 *>(eidx)[c] = src[c];
+}
+constexpr int kLdsBytes = 160 * 1024;  // LDS one workgroup may allocate on gfx950
+
 // Entry loops of the q-derivative sweeps, one instantiation per place the
 // gathered records live (LDS image or memory): a loop whose loads may come
 // from either would be compiled to generic (flat) loads, which go through
@@ -604,8 +620,11 @@ __device__ __forceinline__ int slot_point(const DevCloud &cl, const TileInfo &ti
 
 // first pass: sums of dx dq, dy dq and the componentwise maxima of q and -q
 // over the entries k0 + sub, k0 + sub + kFluxLanes, ... < k1 of point p
-template <bool LDS>
+// SRC 0: records and entry slots in LDS; 1: records in LDS, entry slots from
+// memory; 2: records from memory
+template <int SRC>
 __device__ __forceinline__ void grad0_entries(const DevCloud &cl, const double2 *lds,
+                                              const uint16_t *eidx, int e0,
                                               const double2 *q, int k0, int k1, int sub,
                                               const double qp[4], double2 P, double sx[4],
                                               double sy[4], double mx[4], double mg[4]) {
@@ -613,8 +632,8 @@ __device__ __forceinline__ void grad0_entries(const DevCloud &cl, const double2 
     for (int k = k0 + sub; k < k1; k += kFluxLanes) {
         double qi[4];
         double2 Q;
-        if constexpr (LDS) {
-            const double2 *r = lds + kRec * (int)cl.flidx[k];
+        if constexpr (SRC < 2) {
+            const double2 *r = lds + kRec * (SRC == 0 ? (int)eidx[k - e0] : (int)cl.flidx[k]);
             qi[0] = r[0].x; qi[1] = r[0].y; qi[2] = r[1].x; qi[3] = r[1].y;
             Q = r[2];
         } else {
@@ -648,6 +667,7 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
                                                   Shadow sh) {
     constexpr int kRec = 3;
     extern __shared__ double2 lds[];
+    uint16_t *eidx = reinterpret_cast<uint16_t *>(lds + (size_t)kRec * cap);
     const int t = sweep_tile(cl);
     if (cl.tile_active && !cl.tile_active[t]) return;
     const TileInfo ti = tile_info(cl, t, cap);
@@ -665,6 +685,10 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
         P = cl.xy[p];
         L.load_row(cl.lsi, p, sub);
     }
+    const int e0 = cl.ptr[ti.base], ne = cl.ptr[ti.base + ti.nown] - e0;
+    const int e0a = entry_origin(e0);
+    const bool e_lds = ti.in_lds && e0 + ne - e0a <= kCapE;
+    if (e_lds) stage_entries(cl, eidx, e0, ne);
     if (ti.in_lds) {
         for (int s0 = threadIdx.x; s0 < ti.ns; s0 += kBlock) {
             const int p0 = slot_point(cl, ti, s0);
@@ -691,10 +715,12 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
             mx[r] = qp[r];
             mg[r] = -qp[r];
         }
-        if (ti.in_lds)
-            grad0_entries<true>(cl, lds, q, k0, k1, sub, qp, P, sx, sy, mx, mg);
+        if (e_lds)
+            grad0_entries<0>(cl, lds, eidx, e0a, q, k0, k1, sub, qp, P, sx, sy, mx, mg);
+        else if (ti.in_lds)
+            grad0_entries<1>(cl, lds, eidx, e0a, q, k0, k1, sub, qp, P, sx, sy, mx, mg);
         else
-            grad0_entries<false>(cl, lds, q, k0, k1, sub, qp, P, sx, sy, mx, mg);
+            grad0_entries<2>(cl, lds, eidx, e0a, q, k0, k1, sub, qp, P, sx, sy, mx, mg);
     }
     if (j >= ti.nown) return;  // whole groups of lanes leave
     double gv[2];
@@ -712,22 +738,6 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
         if (sh.qmm32) store_pair(sh.qmm32, p, sub, bv[0], bv[1]);
     }
 }
-
-// entry slots an inner-iteration workgroup stages in LDS (tiles with more
-// entries read them from memory)
-constexpr int kCapE = 2048;
-
-// The tile's entry slots flidx[e0 .. e0 + ne), copied into LDS in 16-byte
-// chunks from the chunk that holds e0 (one load per lane for a tile of 64
-// 24-entry points, where single slots took six dependent rounds); entry k is
-// then at eidx[k - e0a].  The array is padded to a whole chunk.
-__device__ __forceinline__ int entry_origin(int e0) { return e0 & ~7; }
-__device__ __forceinline__ void stage_entries(const DevCloud &cl, uint16_t *eidx, int e0, int ne) {
-    const int e0a = entry_origin(e0), nc = (e0 + ne - e0a + 7) / 8;
-    const uint4 *src = reinterpret_cast<const uint4 *>(cl.flidx + e0a);
-    for (int c = threadIdx.x; c < nc; c += kBlock) reinterpret_cast<uint4 *>(eidx)[c] = src[c];
-}
-constexpr int kLdsBytes = 160 * 1024;  // LDS one workgroup may allocate on gfx950
 
 // inner iteration: sums of dx f, dy f with f = dx g_x,i + dy g_y,i over the
 // entries of point p.  SRC 0: records and entry slots in LDS; 1: records in
@@ -851,11 +861,11 @@ __device__ __forceinline__ void f4_to_d(float4 a, double v[4]) {
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
 }
 
-// first pass over the entries of one point; SRC 0: records in LDS (slot
-// numbers from memory), 2: from memory.  Record: q (float4), position.
+// first pass over the entries of one point; SRC as grad0_entries.  Record: q
+// (float4), position.
 template <int SRC>
 __device__ __forceinline__ void grad0f_entries(const DevCloud &cl, const double2 *lds,
-                                               const float4 *q32, int k0, int k1, int sub,
+                                               const uint16_t *eidx, int e0, const float4 *q32, int k0, int k1, int sub,
                                                const double qp[4], double2 P, double sx[4],
                                                double sy[4], float mx[4], float mg[4]) {
     constexpr int kRec = 2;
@@ -864,8 +874,8 @@ __device__ __forceinline__ void grad0f_entries(const DevCloud &cl, const double2
     for (int k = k0 + sub; k < k1; k += kFluxLanes) {
         float4 a;
         double2 Q;
-        if constexpr (SRC == 0) {
-            const double2 *r = lds + kRec * (int)cl.flidx[k];
+        if constexpr (SRC < 2) {
+            const double2 *r = lds + kRec * (SRC == 0 ? (int)eidx[k - e0] : (int)cl.flidx[k]);
             a = *reinterpret_cast<const float4 *>(r);
             Q = r[1];
         } else {
@@ -936,6 +946,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
                                                     float4 *__restrict__ qmm32, int want_bounds) {
     constexpr int kRec = 2;
     extern __shared__ double2 lds[];
+    uint16_t *eidx = reinterpret_cast<uint16_t *>(lds + (size_t)kRec * cap);
     const int t = sweep_tile(cl);
     if (cl.tile_active && !cl.tile_active[t]) return;
     const TileInfo ti = tile_info(cl, t, cap);
@@ -953,6 +964,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
         a = q32[p];
         L.load_row(cl.lsi, p, sub);
     }
+    const int e0 = cl.ptr[ti.base], ne = cl.ptr[ti.base + ti.nown] - e0;
+    const int e0a = entry_origin(e0);
+    const bool e_lds = ti.in_lds && e0 + ne - e0a <= kCapE;
+    if (e_lds) stage_entries(cl, eidx, e0, ne);
     if (ti.in_lds) {
         for (int s0 = threadIdx.x; s0 < ti.ns; s0 += kBlock) {
             const int p0 = slot_point(cl, ti, s0);
@@ -976,10 +991,12 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
             mx[r] = qf[r];
             mg[r] = -qf[r];
         }
-        if (ti.in_lds)
-            grad0f_entries<0>(cl, lds, q32, k0, k1, sub, qp, P, sx, sy, mx, mg);
+        if (e_lds)
+            grad0f_entries<0>(cl, lds, eidx, e0a, q32, k0, k1, sub, qp, P, sx, sy, mx, mg);
+        else if (ti.in_lds)
+            grad0f_entries<1>(cl, lds, eidx, e0a, q32, k0, k1, sub, qp, P, sx, sy, mx, mg);
         else
-            grad0f_entries<2>(cl, lds, q32, k0, k1, sub, qp, P, sx, sy, mx, mg);
+            grad0f_entries<2>(cl, lds, eidx, e0a, q32, k0, k1, sub, qp, P, sx, sy, mx, mg);
     }
     if (j >= ti.nown) return;  // whole groups of lanes leave
     double gv[2];
@@ -1056,32 +1073,36 @@ static int lds_cap(const DevCloud &c, int budget, int rec) {
 }
 
 // LDS bytes a q-derivative workgroup stages its tile image in when the
-// caller gives no budget (records of 48 and 80 bytes; the inner iteration
-// also stages 4 KB of entry slots).  Sized so that the 6 workgroups per CU
+// caller gives no budget (records of 48 and 80 bytes; 4 KB of entry slots
+// come on top: reading the first pass's slots from memory instead, one dependent
+// load per entry, took 206 us on the 2.5M cloud against 160, on FP32 data 161
+// against 131).  Sized so that the 6 workgroups per CU
 // that the kernels' registers allow stay resident in 160 KB of LDS
 // (measured on the 2.5M cloud: 22 KB runs the inner iteration 12% faster
 // than 36 KB, although a few more tiles then read from memory).
-constexpr int kGrad0Lds = 32 * 1024;
+constexpr int kGrad0Lds = 26 * 1024 - 2 * kCapE;
 constexpr int kGradkLds = 22 * 1024;
 // The FP32-data inner iteration fits 64 VGPRs, i.e. 8 waves per SIMD: 8
 // workgroups per CU when each stays within 20 KB of LDS (images of 48-byte
 // records plus 4 KB of entry slots).  The first pass keeps two entries in
 // flight per lane at 72 VGPRs (7 waves); its images of 32-byte records fit
 // 20 KB as well.
-constexpr int kGrad0FLds = 20 * 1024;
+constexpr int kGrad0FLds = 20 * 1024 - 2 * kCapE;
 constexpr int kGradkFLds = 20 * 1024 - 2 * kCapE;
 
 hipError_t launch_grad0(hipStream_t st, const DevCloud &c, int lds_budget, const double2 *q,
                         double2 *g, double2 *qmm, int want_bounds, Shadow sh) {
     const int rec = 3 * (int)sizeof(double2);
-    const int cap = lds_cap(c, lds_budget > 0 ? lds_budget : kGrad0Lds, rec);
+    const int cap = min(lds_cap(c, lds_budget > 0 ? lds_budget : kGrad0Lds, rec),
+                        (kLdsBytes - 2 * kCapE) / rec);
+    const size_t shmem = cap > 0 ? (size_t)cap * rec + 2 * kCapE : 0;
     const int ntile = sweep_grid(c);
     if (want_bounds && !qmm) {
         if (!sh.qmm32) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_grad0<false>, dim3(ntile), dim3(kBlock), (size_t)cap * rec, st, c, cap,
+        hipLaunchKernelGGL(k_grad0<false>, dim3(ntile), dim3(kBlock), shmem, st, c, cap,
                            q, g, qmm, want_bounds, sh);
     } else {
-        hipLaunchKernelGGL(k_grad0<true>, dim3(ntile), dim3(kBlock), (size_t)cap * rec, st, c, cap,
+        hipLaunchKernelGGL(k_grad0<true>, dim3(ntile), dim3(kBlock), shmem, st, c, cap,
                            q, g, qmm, want_bounds, sh);
     }
     return hipGetLastError();
@@ -1090,8 +1111,10 @@ hipError_t launch_grad0(hipStream_t st, const DevCloud &c, int lds_budget, const
 hipError_t launch_grad0_f(hipStream_t st, const DevCloud &c, int lds_budget, const float4 *q32,
                           float4 *g0f, float4 *qmm32, int want_bounds) {
     const int rec = 2 * (int)sizeof(double2);
-    const int cap = lds_cap(c, lds_budget > 0 ? lds_budget : kGrad0FLds, rec);
-    hipLaunchKernelGGL(k_grad0_f, dim3(sweep_grid(c)), dim3(kBlock), (size_t)cap * rec, st,
+    const int cap = min(lds_cap(c, lds_budget > 0 ? lds_budget : kGrad0FLds, rec),
+                        (kLdsBytes - 2 * kCapE) / rec);
+    const size_t shmem = cap > 0 ? (size_t)cap * rec + 2 * kCapE : 0;
+    hipLaunchKernelGGL(k_grad0_f, dim3(sweep_grid(c)), dim3(kBlock), shmem, st,
                        c, cap, q32, g0f, qmm32, want_bounds);
     return hipGetLastError();
 }
