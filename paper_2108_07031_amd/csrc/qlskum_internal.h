@@ -93,6 +93,21 @@ struct Shadow {
     float4 *qmm32;
 };
 
+// Residual work done by the first nblk workgroups (a multiple of the XCD count)
+// of a first q-derivative pass.  step: 2 chunk sums, 3 norms, 4 row counter;
+// nblk 0: none.
+struct ResRide {
+    int nblk = 0, step = 0, n = 0, nchunk = 0, ncase = 0, cap = 0;
+    const double *R = nullptr;
+    const int *beg = nullptr, *chunk_ptr = nullptr;
+    double *part = nullptr;
+    const int *case_of = nullptr;
+    const uint8_t *active = nullptr;  // nullable: retired cases' chunks are skipped
+    const double *inv_nupd = nullptr;
+    int *ctr = nullptr;
+    double *hist = nullptr;
+};
+
 // Retirement of batched cases, applied on the device after every
 // iteration's residual norms (on = 0: plain iterations).  A case stops
 // (active[c] = 0) at the iteration whose norm is <= *drop * ref[c] (ref[c] < 0
@@ -140,7 +155,8 @@ hipError_t launch_prep(hipStream_t st, const DevCloud &c, const FlowParams &fp, 
 // previous iterate gprev.  gnext may be null when only the FP32 shadow
 // (g32) is wanted, and qmm when only the bounds' FP32 shadow (sh.qmm32) is.
 hipError_t launch_grad0(hipStream_t st, const DevCloud &c, int lds_budget, const double2 *q,
-                        double2 *g, double2 *qmm, int want_bounds, Shadow sh);
+                        double2 *g, double2 *qmm, int want_bounds, Shadow sh,
+                        const ResRide &ride);
 hipError_t launch_gradk(hipStream_t st, const DevCloud &c, int lds_budget, const double2 *g0,
                         const double2 *gprev, double2 *gnext, float4 *g32);
 // mixed precision: the same sweeps gathering FP32 data (q32 for the first
@@ -148,7 +164,7 @@ hipError_t launch_gradk(hipStream_t st, const DevCloud &c, int lds_budget, const
 // positions, differences, sums and solves; FP32 results ([n][2] float4:
 // q_x[0..3], q_y[0..3]; bound offsets qmax - q, qmin - q)
 hipError_t launch_grad0_f(hipStream_t st, const DevCloud &c, int lds_budget, const float4 *q32,
-                          float4 *g0f, float4 *qmm32, int want_bounds);
+                          float4 *g0f, float4 *qmm32, int want_bounds, const ResRide &ride);
 hipError_t launch_gradk_f(hipStream_t st, const DevCloud &c, int lds_budget, const float4 *g0f,
                           const float4 *gprev, float4 *gnext);
 // stage 0: evaluate only (writes Rout); stages 1..4: residual + SSP-RK stage.
@@ -188,7 +204,8 @@ hipError_t launch_wall_distance(hipStream_t st, int n, const double2 *xy, const 
 hipError_t launch_resnorm(hipStream_t st, const double *R, int n, int nchunk, const int *chunk_beg,
                           double *part, int ncase, const int *chunk_ptr, const double *inv_nupd,
                           int *ctr, int cap, double *hist, const Retire &rt,
-                          const int *case_of, uint8_t *tile_active, uint8_t *tile_prec);
+                          const int *case_of, uint8_t *tile_active, uint8_t *tile_prec,
+                          bool chunks_done = false);
 // Fixed device array (kScratchDoubles doubles, per GPU) that holds the
 // residual history of ql_step_static; scratch_address returns its address
 // on the current device.

@@ -30,10 +30,11 @@ namespace ql {
 namespace {
 
 // Workgroups are dispatched to the XCDs round-robin; remap the hardware
-// workgroup id so that XCD x processes one contiguous slice of the grid.
-__device__ __forceinline__ int logical_block() {
-    const int nblk = gridDim.x;
-    const int b = blockIdx.x;
+// workgroup id so that XCD x processes one contiguous slice of the grid (of
+// the workgroups after the first `skip`, a multiple of kXcd).
+__device__ __forceinline__ int logical_block(int skip = 0) {
+    const int nblk = gridDim.x - skip;
+    const int b = blockIdx.x - skip;
     const int q = nblk / kXcd, r = nblk % kXcd;
     const int x = b % kXcd, k = b / kXcd;
     return x * q + (x < r ? x : r) + k;
@@ -41,9 +42,10 @@ __device__ __forceinline__ int logical_block() {
 
 __device__ __forceinline__ int point_id() { return logical_block() * kBlock + threadIdx.x; }
 
-// tile served by this workgroup of a tiled sweep (launched with sweep_grid)
-__device__ __forceinline__ int sweep_tile(const DevCloud &cl) {
-    const int b = logical_block();
+// tile served by this workgroup of a tiled sweep (launched with sweep_grid
+// workgroups after the first `skip`)
+__device__ __forceinline__ int sweep_tile(const DevCloud &cl, int skip = 0) {
+    const int b = logical_block(skip);
     return cl.tile_list ? cl.tile_list[b] : b;
 }
 
@@ -57,6 +59,97 @@ __device__ __forceinline__ void report(ErrWord *err, int p, int code) {
 __device__ __forceinline__ void report_pt(const DevCloud &cl, ErrWord *err, int p, int code) {
     report(err, p, code);
     if (cl.case_err) report(cl.case_err + cl.case_of[p], p, code);
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// LDS of a residual workgroup: the wavefronts' partial sums, a case's norms
+struct ResLds {
+    double red[kBlock / 64][4];
+    double nv[4];
+};
+
+// squares of R over chunk ch (see k_res_chunks)
+__device__ __forceinline__ void res_chunk(ResLds &sh, const double *__restrict__ R, int n,
+                                          const int *__restrict__ beg, double *__restrict__ part,
+                                          const int *__restrict__ case_of,
+                                          const uint8_t *__restrict__ active, int ch) {
+    const int b = beg[ch], e = beg[ch + 1];
+    if (active && b < e && !active[case_of[b]]) return;
+    double acc[4] = {0, 0, 0, 0};
+    for (int p = b + threadIdx.x; p < e; p += kBlock) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const double r = R[(size_t)c * n + p];
+            acc[c] += r * r;
+        }
+    }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const double t = wave_sum(acc[c]);
+        if (lane == 0) sh.red[wv][c] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < kBlock / 64; ++j) t += sh.red[j][threadIdx.x];
+        part[4 * ch + threadIdx.x] = t;
+    }
+}
+
+// norms of case cs from its chunk sums, into history row `row`
+__device__ __forceinline__ void res_case(ResLds &sh, int ncase, const int *__restrict__ chunk_ptr,
+                                         const double *__restrict__ part,
+                                         const double *__restrict__ inv_nupd, int row, int cap,
+                                         double *__restrict__ hist, int cs) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double acc[4] = {0, 0, 0, 0};
+    for (int j = chunk_ptr[cs] + threadIdx.x; j < chunk_ptr[cs + 1]; j += kBlock) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] += part[4 * j + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const double t = wave_sum(acc[c]);
+        if (lane == 0) sh.red[wv][c] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < kBlock / 64; ++j) t += sh.red[j][threadIdx.x];
+        const double v = sqrt(t * inv_nupd[cs]);
+        if (row < cap) hist[((size_t)row * ncase + cs) * 4 + threadIdx.x] = v;
+        sh.nv[threadIdx.x] = v;
+    }
+    __syncthreads();
+}
+
+// The residual norms as extra workgroups of the first q-derivative passes of
+// stages 2 to 4: stage 1 leaves R, and the norms are only read after the
+// iteration, so they need no launches of their own (two of an iteration's 22,
+// ~4.5 us each, and reading R meanwhile costs no time of its own: 2.97 -> 2.73 ms for 20
+// iterations at 9.6k points, 2.58 -> 2.51 at 41k).  The stages' launches order
+// the steps: chunk sums (stage 2), norms (stage 3), row counter (stage 4).  The
+// residual workgroups come first in the grid, so that a large cloud has no tail
+// of them, and are a multiple of the XCDs, so that a tile stays on its XCD.
+__device__ __forceinline__ void res_ride(const ResRide &r, ResLds &sh) {
+    const int b = blockIdx.x;
+    if (r.step == 2) {
+        if (b < r.nchunk)
+            res_chunk(sh, r.R, r.n, r.beg, r.part, r.case_of, r.active, b);
+    } else if (r.step == 3) {
+        if (b < r.ncase)
+            res_case(sh, r.ncase, r.chunk_ptr, r.part, r.inv_nupd, *r.ctr, r.cap, r.hist, b);
+    } else if (b == 0 && threadIdx.x == 0) {
+        *r.ctr += 1;
+    }
 }
 
 __device__ __forceinline__ void load4(const double2 *a, int p, double v[4]) {
@@ -664,11 +757,16 @@ __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
                                                   const double2 *__restrict__ q,
                                                   double2 *__restrict__ g,
                                                   double2 *__restrict__ qmm, int want_bounds,
-                                                  Shadow sh) {
+                                                  Shadow sh, ResRide ride) {
     constexpr int kRec = 3;
     extern __shared__ double2 lds[];
+    __shared__ ResLds rlds;
+    if ((int)blockIdx.x < ride.nblk) {
+        res_ride(ride, rlds);
+        return;
+    }
     uint16_t *eidx = reinterpret_cast<uint16_t *>(lds + (size_t)kRec * cap);
-    const int t = sweep_tile(cl);
+    const int t = sweep_tile(cl, ride.nblk);
     if (cl.tile_active && !cl.tile_active[t]) return;
     const TileInfo ti = tile_info(cl, t, cap);
     const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
@@ -943,11 +1041,17 @@ __device__ __forceinline__ double2 lane_pair(const float4 *g, int p, int sub) {
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) k_grad0_f(DevCloud cl, int cap,
                                                     const float4 *__restrict__ q32,
                                                     float4 *__restrict__ g0f,
-                                                    float4 *__restrict__ qmm32, int want_bounds) {
+                                                    float4 *__restrict__ qmm32, int want_bounds,
+                                                    ResRide ride) {
     constexpr int kRec = 2;
     extern __shared__ double2 lds[];
+    __shared__ ResLds rlds;
+    if ((int)blockIdx.x < ride.nblk) {
+        res_ride(ride, rlds);
+        return;
+    }
     uint16_t *eidx = reinterpret_cast<uint16_t *>(lds + (size_t)kRec * cap);
-    const int t = sweep_tile(cl);
+    const int t = sweep_tile(cl, ride.nblk);
     if (cl.tile_active && !cl.tile_active[t]) return;
     const TileInfo ti = tile_info(cl, t, cap);
     const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
@@ -1091,31 +1195,32 @@ constexpr int kGrad0FLds = 20 * 1024 - 2 * kCapE;
 constexpr int kGradkFLds = 20 * 1024 - 2 * kCapE;
 
 hipError_t launch_grad0(hipStream_t st, const DevCloud &c, int lds_budget, const double2 *q,
-                        double2 *g, double2 *qmm, int want_bounds, Shadow sh) {
+                        double2 *g, double2 *qmm, int want_bounds, Shadow sh,
+                        const ResRide &ride) {
     const int rec = 3 * (int)sizeof(double2);
     const int cap = min(lds_cap(c, lds_budget > 0 ? lds_budget : kGrad0Lds, rec),
-                        (kLdsBytes - 2 * kCapE) / rec);
+                        (kLdsBytes - 2 * kCapE - (int)sizeof(ResLds)) / rec);
     const size_t shmem = cap > 0 ? (size_t)cap * rec + 2 * kCapE : 0;
-    const int ntile = sweep_grid(c);
+    const int nblk = sweep_grid(c) + ride.nblk;
     if (want_bounds && !qmm) {
         if (!sh.qmm32) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_grad0<false>, dim3(ntile), dim3(kBlock), shmem, st, c, cap,
-                           q, g, qmm, want_bounds, sh);
+        hipLaunchKernelGGL(k_grad0<false>, dim3(nblk), dim3(kBlock), shmem, st, c, cap,
+                           q, g, qmm, want_bounds, sh, ride);
     } else {
-        hipLaunchKernelGGL(k_grad0<true>, dim3(ntile), dim3(kBlock), shmem, st, c, cap,
-                           q, g, qmm, want_bounds, sh);
+        hipLaunchKernelGGL(k_grad0<true>, dim3(nblk), dim3(kBlock), shmem, st, c, cap,
+                           q, g, qmm, want_bounds, sh, ride);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_grad0_f(hipStream_t st, const DevCloud &c, int lds_budget, const float4 *q32,
-                          float4 *g0f, float4 *qmm32, int want_bounds) {
+                          float4 *g0f, float4 *qmm32, int want_bounds, const ResRide &ride) {
     const int rec = 2 * (int)sizeof(double2);
     const int cap = min(lds_cap(c, lds_budget > 0 ? lds_budget : kGrad0FLds, rec),
-                        (kLdsBytes - 2 * kCapE) / rec);
+                        (kLdsBytes - 2 * kCapE - (int)sizeof(ResLds)) / rec);
     const size_t shmem = cap > 0 ? (size_t)cap * rec + 2 * kCapE : 0;
-    hipLaunchKernelGGL(k_grad0_f, dim3(sweep_grid(c)), dim3(kBlock), shmem, st,
-                       c, cap, q32, g0f, qmm32, want_bounds);
+    hipLaunchKernelGGL(k_grad0_f, dim3(sweep_grid(c) + ride.nblk), dim3(kBlock), shmem, st,
+                       c, cap, q32, g0f, qmm32, want_bounds, ride);
     return hipGetLastError();
 }
 
@@ -1334,12 +1439,6 @@ __device__ __forceinline__ void venkat2(double da, const double *ba, double db, 
     const double r = fast_rcp(ga * gb);
     pa = na * (r * gb);
     pb = nb * (r * ga);
-}
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
 }
 
 // Contribution of one neighbour entry (split flags f, offset (dx, dy) from p
@@ -2476,31 +2575,8 @@ __global__ void __launch_bounds__(kBlock) k_res_chunks(const double *__restrict_
                                                        double *__restrict__ part,
                                                        const int *__restrict__ case_of,
                                                        const uint8_t *__restrict__ active) {
-    __shared__ double red[kBlock / 64][4];
-    const int ch = blockIdx.x;
-    const int b = beg[ch], e = beg[ch + 1];
-    if (active && b < e && !active[case_of[b]]) return;
-    double acc[4] = {0, 0, 0, 0};
-    for (int p = b + threadIdx.x; p < e; p += kBlock) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const double r = R[(size_t)c * n + p];
-            acc[c] += r * r;
-        }
-    }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const double t = wave_sum(acc[c]);
-        if (lane == 0) red[wv][c] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x < 4) {
-        double t = 0.0;
-#pragma unroll
-        for (int j = 0; j < kBlock / 64; ++j) t += red[j][threadIdx.x];
-        part[4 * ch + threadIdx.x] = t;
-    }
+    __shared__ ResLds sh;
+    res_chunk(sh, R, n, beg, part, case_of, active, blockIdx.x);
 }
 
 __global__ void __launch_bounds__(kBlock) k_res_cases(int ncase, const int *__restrict__ chunk_ptr,
@@ -2508,49 +2584,28 @@ __global__ void __launch_bounds__(kBlock) k_res_cases(int ncase, const int *__re
                                                       const double *__restrict__ inv_nupd,
                                                       int *ctr, int cap,
                                                       double *__restrict__ hist, Retire rt) {
-    __shared__ double red[kBlock / 64][4];
-    __shared__ double nv[4];
+    __shared__ ResLds sh;
     const int row = *ctr;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const double drop = rt.on ? *rt.drop : 0.0;
     // workgroup cs takes case cs (one workgroup: every case in turn, and it
     // advances the row counter itself)
     for (int cs = blockIdx.x; cs < ncase; cs += gridDim.x) {
         if (rt.on && !rt.active[cs]) continue;
-        double acc[4] = {0, 0, 0, 0};
-        for (int j = chunk_ptr[cs] + threadIdx.x; j < chunk_ptr[cs + 1]; j += kBlock) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] += part[4 * j + c];
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const double t = wave_sum(acc[c]);
-            if (lane == 0) red[wv][c] = t;
-        }
-        __syncthreads();
-        if (threadIdx.x < 4) {
-            double t = 0.0;
-#pragma unroll
-            for (int j = 0; j < kBlock / 64; ++j) t += red[j][threadIdx.x];
-            const double v = sqrt(t * inv_nupd[cs]);
-            if (row < cap) hist[((size_t)row * ncase + cs) * 4 + threadIdx.x] = v;
-            nv[threadIdx.x] = v;
-        }
-        __syncthreads();
+        res_case(sh, ncase, chunk_ptr, part, inv_nupd, row, cap, hist, cs);
         // retirement: this iteration's norms are those of the state it
         // started from, and the state it leaves is the one a case keeps
         if (rt.on && threadIdx.x == 0 && rt.active[cs]) {
             rt.iters[cs] += 1;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) rt.last[4 * cs + c] = nv[c];
+            for (int c = 0; c < 4; ++c) rt.last[4 * cs + c] = sh.nv[c];
             double ref = rt.ref[cs];
-            if (ref < 0.0) ref = rt.ref[cs] = nv[0];
-            if (rt.prec && rt.prec[cs] && nv[0] <= *rt.sw * ref) {
+            if (ref < 0.0) ref = rt.ref[cs] = sh.nv[0];
+            if (rt.prec && rt.prec[cs] && sh.nv[0] <= *rt.sw * ref) {
                 rt.prec[cs] = 0;
                 rt.sw_iter[cs] = rt.iters[cs];
             }
-            if (rt.case_err[cs] != kErrClear || nv[0] <= drop * ref ||
-                nv[0] > kDiverged * ref || !(nv[0] == nv[0]))
+            if (rt.case_err[cs] != kErrClear || sh.nv[0] <= drop * ref ||
+                sh.nv[0] > kDiverged * ref || !(sh.nv[0] == sh.nv[0]))
                 rt.active[cs] = 0;
         }
     }
@@ -2558,17 +2613,21 @@ __global__ void __launch_bounds__(kBlock) k_res_cases(int ncase, const int *__re
 }
 
 // advances the history row counter after a k_res_cases of several workgroups
+// (no retirement)
 __global__ void k_res_advance(int *ctr) { *ctr += 1; }
 
 // tile t is skipped by every tiled sweep when no case it holds is active;
 // its split fluxes are FP32 only while every case it holds is (case_prec
-// nullable: no precision switch)
+// nullable: no precision switch).  It also advances the history row counter of
+// a batch (ctr nullable: k_res_cases did)
 __global__ void __launch_bounds__(kBlock) k_tile_active(int n, int ntile,
                                                         const int *__restrict__ case_of,
                                                         const uint8_t *__restrict__ case_active,
                                                         uint8_t *__restrict__ tile_active,
                                                         const uint8_t *__restrict__ case_prec,
-                                                        uint8_t *__restrict__ tile_prec) {
+                                                        uint8_t *__restrict__ tile_prec,
+                                                        int *ctr) {
+    if (ctr && blockIdx.x == 0 && threadIdx.x == 0) *ctr += 1;
     const int t = blockIdx.x * kBlock + threadIdx.x;
     if (t >= ntile) return;
     const int b = t * kFluxTile, e = min(n, b + kFluxTile) - 1;
@@ -2584,16 +2643,20 @@ __global__ void __launch_bounds__(kBlock) k_tile_active(int n, int ntile,
 hipError_t launch_resnorm(hipStream_t st, const double *R, int n, int nchunk, const int *chunk_beg,
                           double *part, int ncase, const int *chunk_ptr, const double *inv_nupd,
                           int *ctr, int cap, double *hist, const Retire &rt,
-                          const int *case_of, uint8_t *tile_active, uint8_t *tile_prec) {
-    hipLaunchKernelGGL(k_res_chunks, dim3(nchunk), dim3(kBlock), 0, st, R, n, chunk_beg, part,
-                       case_of, rt.on ? rt.active : nullptr);
+                          const int *case_of, uint8_t *tile_active, uint8_t *tile_prec,
+                          bool chunks_done) {
+    if (!chunks_done)
+        hipLaunchKernelGGL(k_res_chunks, dim3(nchunk), dim3(kBlock), 0, st, R, n, chunk_beg, part,
+                           case_of, rt.on ? rt.active : nullptr);
     hipLaunchKernelGGL(k_res_cases, dim3(ncase), dim3(kBlock), 0, st, ncase, chunk_ptr, part,
                        inv_nupd, ctr, cap, hist, rt);
-    if (ncase > 1) hipLaunchKernelGGL(k_res_advance, dim3(1), dim3(1), 0, st, ctr);
     if (rt.on) {
         const int ntile = num_flux_tiles(n);
         hipLaunchKernelGGL(k_tile_active, dim3((ntile + kBlock - 1) / kBlock), dim3(kBlock), 0, st,
-                           n, ntile, case_of, rt.active, tile_active, rt.prec, tile_prec);
+                           n, ntile, case_of, rt.active, tile_active, rt.prec, tile_prec,
+                           ncase > 1 ? ctr : nullptr);
+    } else if (ncase > 1) {
+        hipLaunchKernelGGL(k_res_advance, dim3(1), dim3(1), 0, st, ctr);
     }
     return hipGetLastError();
 }

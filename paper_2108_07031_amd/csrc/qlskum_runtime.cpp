@@ -545,7 +545,8 @@ struct Timer {
 // also write the FP32 copies the mixed flux sweep reads, and skip the FP64
 // bounds and final iterate that only inspection (fp64_out) or a run that
 // switches cases to FP64 fluxes reads.
-int run_gradients(ql_solver *s, const DevCloud &c, bool want_bounds, bool fp64_out) {
+int run_gradients(ql_solver *s, const DevCloud &c, bool want_bounds, bool fp64_out,
+                  const ResRide &ride = {}) {
     const bool mixed = s->prm.precision == 1;
     s->grad_f32 = mixed && !s->hybrid && s->prm.mixed_grad == 0;
     if (s->grad_f32) {
@@ -553,7 +554,8 @@ int run_gradients(ql_solver *s, const DevCloud &c, bool want_bounds, bool fp64_o
         {
             Timer t(s, 0);
             HIPCHK(s, launch_grad0_f(s->stream, c, s->prm.grad_lds, s->q32[s->qcur],
-                                     ni > 0 ? s->gf[0] : s->g32, s->qmm32, want_bounds ? 1 : 0));
+                                     ni > 0 ? s->gf[0] : s->g32, s->qmm32, want_bounds ? 1 : 0,
+                                     ride));
             t.done();
         }
         const float4 *cur = s->gf[0];
@@ -576,7 +578,7 @@ int run_gradients(ql_solver *s, const DevCloud &c, bool want_bounds, bool fp64_o
     {
         Timer t(s, 0);
         HIPCHK(s, launch_grad0(s->stream, c, s->prm.grad_lds, s->q[s->qcur], s->g[first],
-                               skip64 ? nullptr : s->qmm, want_bounds ? 1 : 0, sh));
+                               skip64 ? nullptr : s->qmm, want_bounds ? 1 : 0, sh, ride));
         t.done();
     }
     int cur = first;
@@ -642,27 +644,44 @@ int launch_stage(ql_solver *s, const DevCloud &c, const FlowParams &fp, int stag
     return QL_OK;
 }
 
-// Enqueue one pseudo-time iteration: four stages, then the residual norms of
-// stage 1 into history row *ctr.
+// Enqueue one pseudo-time iteration: four stages, and the residual norms of
+// stage 1 into history row *ctr.  Second order: the norms ride in the first
+// q-derivative passes of stages 2 to 4 (in a batch that retires cases only
+// their chunk sums, since retirement looks at the state after stage 4); timed
+// iterations launch them by themselves, as the first-order scheme does.
 int enqueue_iteration(ql_solver *s, const DevCloud &c, const FlowParams &fp, int hist_cap,
                       double *hist) {
+    const bool ride = fp.order == 2 && (!s->timing || s->capturing || s->no_alloc);
+    const double *inv_nupd = s->inv_nupd + (fp.kobc ? s->ncase : 0);
     for (int rk = 1; rk <= 4; ++rk) {
         int st = QL_OK;
+        ResRide r;
+        if (ride && (rk == 2 || (rk > 2 && !s->retire_on))) {
+            const int nblk = rk == 2 ? s->nchunk : rk == 3 ? s->ncase : 1;
+            r.nblk = (nblk + kXcd - 1) / kXcd * kXcd;
+            r.step = rk;
+            r.n = s->n; r.nchunk = s->nchunk; r.ncase = s->ncase; r.cap = hist_cap;
+            r.R = s->R; r.beg = s->chunk_beg; r.chunk_ptr = s->chunk_ptr; r.part = s->part;
+            r.case_of = s->case_of;
+            r.active = s->retire_on ? s->case_active : nullptr;
+            r.inv_nupd = inv_nupd; r.ctr = s->ctr; r.hist = hist;
+        }
         // the first-order scheme needs no q-derivatives
-        if (fp.order == 2 && (st = run_gradients(s, c, fp.limiter != 0, false))) return st;
+        if (fp.order == 2 && (st = run_gradients(s, c, fp.limiter != 0, false, r))) return st;
         Timer t(s, 2);
         st = launch_stage(s, c, fp, rk, rk == 1 ? s->R : nullptr);
         if (st) return st;
         t.done();
         s->qcur = 1 - s->qcur;
     }
+    if (ride && !s->retire_on) return QL_OK;
     Timer t(s, 3);
     const Retire rt{s->retire_on ? 1 : 0, s->bt_drop, s->bt_ref, s->bt_iters, s->bt_last,
                     s->case_active, s->case_err, s->bt_switch,
                     s->hybrid ? s->case_prec : nullptr, s->bt_swit};
     HIPCHK(s, launch_resnorm(s->stream, s->R, s->n, s->nchunk, s->chunk_beg, s->part, s->ncase,
-                             s->chunk_ptr, s->inv_nupd + (fp.kobc ? s->ncase : 0), s->ctr,
-                             hist_cap, hist, rt, s->case_of, s->tile_active, s->tile_prec));
+                             s->chunk_ptr, inv_nupd, s->ctr, hist_cap, hist, rt, s->case_of,
+                             s->tile_active, s->tile_prec, ride));
     t.done();
     return QL_OK;
 }
