@@ -1945,6 +1945,7 @@ __device__ __forceinline__ Prim first_order_prim(const double2 *q, int i, const 
 }
 
 constexpr int kFirstRec = 5;
+constexpr int kFirstOwnLds = kFluxTile * 8 * (int)sizeof(double2);  // G0 of k_flux_first
 
 // the lane's entries, IN_LDS as in flux_point; G0 holds the point's own split
 // fluxes G_s+, G_s-, G_n+, G_n-
@@ -2125,7 +2126,9 @@ hipError_t launch_flux(hipStream_t st, const DevCloud &c, const FlowParams &fp, 
                        float4 *q32next, ErrWord *err, int split, double *const Rpart[2]) {
     const bool first = fp.order == 1;
     const int rec = (first ? kFirstRec : fp.limiter ? 11 : 7) * (int)sizeof(double2);
-    const int cap = lds_cap(c, lds_budget, rec);
+    // the first-order image shares the workgroup's LDS with the points' own fluxes
+    const int cap = min(lds_cap(c, lds_budget, rec),
+                        (kLdsBytes - (first ? kFirstOwnLds : 0)) / rec);
     const size_t shmem = (size_t)cap * rec;
     const dim3 grid(sweep_grid(c)), block(kBlock);
     auto go = [&](auto kern, int stg, const double *rin, double *rout) {

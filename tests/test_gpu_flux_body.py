@@ -66,3 +66,23 @@ def test_first_order_records(ql, gamma, outer_bc):
     for o in out[1:]:
         for a, b in zip(o, out[0]):
             np.testing.assert_array_equal(a, b)
+
+
+def test_first_order_full_lds(ql):
+    """First order with the whole LDS as the budget, on tiles whose images ask
+    for more of it than the kernel's own arrays leave (then read from memory)."""
+    from cloudgen import random_cloud
+    print("first order full LDS", flush=True)
+    c = random_cloud(6000, seed=7, k=40)
+    src = np.repeat(np.arange(c.n) // 64, np.diff(c.nbr_ptr))
+    slots = [len(set(c.nbr_idx[src == t]) | set(range(64 * t, min(64 * t + 64, c.n))))
+             for t in range(8)]
+    assert any(80 * k <= 160 * 1024 < 80 * k + 8192 for k in slots) and max(slots) * 80 > 152 * 1024
+    U = smooth_state(c, mach=0.5, alpha_deg=1.0)
+    out = []
+    for b in (16, 160 * 1024):
+        s = ql.Solver(c, mach=0.5, alpha_deg=1.0, order=1, flux_lds=b, reorder=0)
+        s.set_state(U)
+        out.append(s.evaluate()["R"])
+        s.close()
+    np.testing.assert_array_equal(out[0], out[1])
