@@ -94,7 +94,7 @@ struct Shadow {
 };
 
 // Residual work done by the first nblk workgroups (a multiple of the XCD count)
-// of a first q-derivative pass.  step: 2 chunk sums, 3 norms, 4 row counter;
+// of a first q-derivative pass or an FP64 first-order flux sweep.  step: 2 chunk sums, 3 norms, 4 row counter;
 // nblk 0: none.
 struct ResRide {
     int nblk = 0, step = 0, n = 0, nchunk = 0, ncase = 0, cap = 0;
@@ -177,7 +177,8 @@ hipError_t launch_gradk_f(hipStream_t st, const DevCloud &c, int lds_budget, con
 hipError_t launch_flux(hipStream_t st, const DevCloud &c, const FlowParams &fp, int stage,
                        int lds_budget, const double2 *q, const double2 *g, const double2 *qmm,
                        double *U, double *Un, double *dt, double2 *qnext, double *Rout,
-                       float4 *q32next, ErrWord *err, int split, double *const Rpart[2]);
+                       float4 *q32next, ErrWord *err, int split, double *const Rpart[2],
+                       const ResRide &ride = {});  // ride: first order only
 // mixed precision: reconstruction, limiter and split fluxes in FP32 from the
 // shadows q32, g32, qmm32; weights, residual sums and the update in FP64.
 hipError_t launch_flux_mixed(hipStream_t st, const DevCloud &c, const FlowParams &fp, int stage,

@@ -131,11 +131,12 @@ __device__ __forceinline__ void res_case(ResLds &sh, int ncase, const int *__res
     __syncthreads();
 }
 
-// The residual norms as extra workgroups of the first q-derivative passes of
-// stages 2 to 4: stage 1 leaves R, and the norms are only read after the
+// The residual norms as extra workgroups of the first q-derivative passes (first
+// order: of the flux sweeps) of stages 2 to 4: stage 1 leaves R, and the norms are only read after the
 // iteration, so they need no launches of their own (two of an iteration's 22,
 // ~4.5 us each, and reading R meanwhile costs no time of its own: 2.97 -> 2.73 ms for 20
-// iterations at 9.6k points, 2.58 -> 2.51 at 41k).  The stages' launches order
+// iterations at 9.6k points, 2.58 -> 2.51 for 10 at 41k; a first-order iteration at
+// 9.6k 46.9 -> 36.4 us, at 144k 155 -> 143).  The stages' launches order
 // the steps: chunk sums (stage 2), norms (stage 3), row counter (stage 4).  The
 // residual workgroups come first in the grid, so that a large cloud has no tail
 // of them, and are a multiple of the XCDs, so that a tile stays on its XCD.
@@ -2039,10 +2040,15 @@ __global__ void __launch_bounds__(kBlock)
 k_flux_first(DevCloud cl, FlowParams fp, int stage, int cap, const double2 *__restrict__ q,
              double *__restrict__ U, double *__restrict__ Un, double *__restrict__ dt,
              double2 *__restrict__ qnext, double *__restrict__ Rout, float4 *__restrict__ q32next,
-             ErrWord *err) {
+             ErrWord *err, ResRide ride) {
     extern __shared__ double2 lds[];
     __shared__ double2 G0[kFluxTile][8];
-    const int t = sweep_tile(cl);
+    static_assert(sizeof(ResLds) <= sizeof(G0), "the residual workgroups use G0");
+    if ((int)blockIdx.x < ride.nblk) {
+        res_ride(ride, *reinterpret_cast<ResLds *>(G0));
+        return;
+    }
+    const int t = sweep_tile(cl, ride.nblk);
     if (cl.tile_active && !cl.tile_active[t]) return;
     if (cl.tile_prec && cl.tile_prec[t] != 0) return;  // an FP32-flux tile
     const TileInfo ti = tile_info(cl, t, cap);
@@ -2123,7 +2129,8 @@ void dispatch_flow(const FlowParams &fp, F &&f) {
 hipError_t launch_flux(hipStream_t st, const DevCloud &c, const FlowParams &fp, int stage,
                        int lds_budget, const double2 *q, const double2 *g, const double2 *qmm,
                        double *U, double *Un, double *dt, double2 *qnext, double *Rout,
-                       float4 *q32next, ErrWord *err, int split, double *const Rpart[2]) {
+                       float4 *q32next, ErrWord *err, int split, double *const Rpart[2],
+                       const ResRide &ride) {
     const bool first = fp.order == 1;
     const int rec = (first ? kFirstRec : fp.limiter ? 11 : 7) * (int)sizeof(double2);
     // the first-order image shares the workgroup's LDS with the points' own fluxes
@@ -2137,8 +2144,8 @@ hipError_t launch_flux(hipStream_t st, const DevCloud &c, const FlowParams &fp, 
     };
     if (first) {  // one fused launch
         auto go1 = [&](auto kern) {
-            hipLaunchKernelGGL(kern, grid, block, shmem, st, c, fp, stage, cap, q, U, Un, dt, qnext,
-                               Rout, q32next, err);
+            hipLaunchKernelGGL(kern, dim3(grid.x + ride.nblk), block, shmem, st, c, fp, stage, cap,
+                               q, U, Un, dt, qnext, Rout, q32next, err, ride);
         };
         if (fp.sqrt_pow == 5) {
             if (fp.kobc) go1(k_flux_first<5, true>);

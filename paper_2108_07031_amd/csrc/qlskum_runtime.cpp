@@ -616,7 +616,8 @@ int flux_lds_budget(const ql_solver *s) {
 }
 
 // One flux-residual launch (stage 0: evaluate into R; 1..4: RK stage).
-int launch_stage(ql_solver *s, const DevCloud &c, const FlowParams &fp, int stage, double *Rout) {
+int launch_stage(ql_solver *s, const DevCloud &c, const FlowParams &fp, int stage, double *Rout,
+                 const ResRide &ride = {}) {
     const int a = s->qcur, b = 1 - s->qcur;
     const int lds = flux_lds_budget(s);
     if (s->hybrid) {
@@ -627,7 +628,8 @@ int launch_stage(ql_solver *s, const DevCloud &c, const FlowParams &fp, int stag
         const int lds64 = flux_lds_budget(s);
         s->prm = saved;
         HIPCHK(s, launch_flux(s->stream, c, fp, stage, lds64, s->q[a], s->g[s->gfin], s->qmm, s->U,
-                              s->Un, s->dt, s->q[b], Rout, s->q32[b], s->errw, 0, s->Rpart));
+                              s->Un, s->dt, s->q[b], Rout, s->q32[b], s->errw, 0, s->Rpart,
+                              ride));
         HIPCHK(s, launch_flux_mixed(s->stream, c, fp, stage, lds, s->q[a], s->q32[a], s->g32,
                                     s->qmm32, s->U, s->Un, s->dt, s->q[b], s->q32[b], Rout,
                                     s->errw));
@@ -640,18 +642,20 @@ int launch_stage(ql_solver *s, const DevCloud &c, const FlowParams &fp, int stag
     else
         HIPCHK(s, launch_flux(s->stream, c, fp, stage, lds, s->q[a], s->g[s->gfin], s->qmm, s->U,
                               s->Un, s->dt, s->q[b], Rout, s->q32[b], s->errw,
-                              fp.order == 2 ? 2 * s->prm.flux_split : 0, s->Rpart));
+                              fp.order == 2 ? 2 * s->prm.flux_split : 0, s->Rpart, ride));
     return QL_OK;
 }
 
 // Enqueue one pseudo-time iteration: four stages, and the residual norms of
-// stage 1 into history row *ctr.  Second order: the norms ride in the first
-// q-derivative passes of stages 2 to 4 (in a batch that retires cases only
-// their chunk sums, since retirement looks at the state after stage 4); timed
-// iterations launch them by themselves, as the first-order scheme does.
+// stage 1 into history row *ctr.  The norms ride in the first q-derivative
+// passes of stages 2 to 4, first order in the FP64 flux sweeps (in a batch that
+// retires cases only their chunk sums, since retirement looks at the state
+// after stage 4); timed iterations and the FP32 first-order sweep leave them to
+// launches of their own.
 int enqueue_iteration(ql_solver *s, const DevCloud &c, const FlowParams &fp, int hist_cap,
                       double *hist) {
-    const bool ride = fp.order == 2 && (!s->timing || s->capturing || s->no_alloc);
+    const bool ride = (fp.order == 2 || s->prm.precision == 0 || s->hybrid) &&
+                      (!s->timing || s->capturing || s->no_alloc);
     const double *inv_nupd = s->inv_nupd + (fp.kobc ? s->ncase : 0);
     for (int rk = 1; rk <= 4; ++rk) {
         int st = QL_OK;
@@ -669,7 +673,7 @@ int enqueue_iteration(ql_solver *s, const DevCloud &c, const FlowParams &fp, int
         // the first-order scheme needs no q-derivatives
         if (fp.order == 2 && (st = run_gradients(s, c, fp.limiter != 0, false, r))) return st;
         Timer t(s, 2);
-        st = launch_stage(s, c, fp, rk, rk == 1 ? s->R : nullptr);
+        st = launch_stage(s, c, fp, rk, rk == 1 ? s->R : nullptr, fp.order == 1 ? r : ResRide{});
         if (st) return st;
         t.done();
         s->qcur = 1 - s->qcur;
