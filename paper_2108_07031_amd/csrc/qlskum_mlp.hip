@@ -346,7 +346,9 @@ hipError_t launch_weights_bf16(hipStream_t st, int fi, int fo, const float *W, b
 // ---------------------------------------------------------------------------
 namespace {
 
-constexpr int kLd = kFuseWidth + 8;  // LDS row: 272 bytes, 16 rows on distinct banks
+// LDS row of a network of widths up to W: 16 bytes more than a power of two, 16
+// rows on distinct banks
+constexpr int lds_row(int W) { return W + 8; }
 constexpr int kFrag = 16 * 32;       // elements of a fragment
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -358,13 +360,15 @@ __device__ __forceinline__ size_t frag_index(int c, int k, int steps) {
            (k & 7);
 }
 
-// 16 x 16 block: rows of A in LDS (leading dimension kLd, zero past K), columns
-// b of B, K in ks steps of 32
-__device__ __forceinline__ f32x4 block_product(const bf16 *A, const bf16x8 b[4], int ks, int lane) {
+// 16 x 16 block: rows of A in LDS (leading dimension lds_row(W), zero past K),
+// columns b of B, K in ks steps of 32
+template <int W>
+__device__ __forceinline__ f32x4 block_product(const bf16 *A, const bf16x8 b[W / 32], int ks,
+                                               int lane) {
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    const bf16 *r = A + (lane & 15) * kLd + 8 * (lane >> 4);
+    const bf16 *r = A + (lane & 15) * lds_row(W) + 8 * (lane >> 4);
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int s = 0; s < W / 32; ++s)
         if (s < ks)
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                 *reinterpret_cast<const bf16x8 *>(r + 32 * s), b[s], acc, 0, 0, 0);
@@ -380,15 +384,17 @@ __device__ __forceinline__ f32x4 block_product(const bf16 *A, const bf16x8 b[4],
 // multiply-adds on the matrix cores.  640,000 rows 279 us; layer by layer it took
 // six kernels per max_batch rows, with every activation through memory twice
 // (2033 us).
+// W: the widths' limit, 128 or 256 (a narrow network would hold the wider form's
+// operand registers and LDS rows without using them).
 // TRAIN: the same, then the output error and the errors of every layer back to
 // the first (each row's own).  a_l and d_l are left in memory as fragments along
 // the batch, zero past row n: a lane's four results are consecutive rows of one
 // column, and the wavefront's 8-byte stores fill 512 bytes in a row.
-template <int MB, int NW, bool TRAIN>
+template <int W, int MB, int NW, bool TRAIN>
 __global__ void __launch_bounds__(64 * NW)
     k_mlp_rows(MlpNet net, int64_t n, const float *__restrict__ X, const float *__restrict__ T,
                float *__restrict__ Y, float scale, float *__restrict__ losspart) {
-    constexpr int MT = 16 * MB;
+    constexpr int MT = 16 * MB, kLd = lds_row(W), KS = W / 32;
     extern __shared__ __align__(16) bf16 sm[];
     auto buf = [&](int i) { return sm + i * MT * kLd; };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -397,7 +403,7 @@ __global__ void __launch_bounds__(64 * NW)
     const int rows = (int)max((int64_t)0, min((int64_t)MT, n - r0));
     // this wavefront's block t of step s: the forward layers 0 .. L-1, then the
     // layers L-1 .. 1 backward
-    auto fetch = [&](int s, int t, bf16x8 b[4], float &bias) {
+    auto fetch = [&](int s, int t, bf16x8 b[KS], float &bias) {
         const bool fwd = s < net.L;
         const int l = fwd ? s : 2 * net.L - 1 - s;
         const int K = net.w[fwd ? l : l + 1], N = net.w[fwd ? l + 1 : l], c = 16 * t + col;
@@ -405,7 +411,7 @@ __global__ void __launch_bounds__(64 * NW)
         const bf16 *P = (fwd ? net.Wf[l] : net.Wr[l]) + (size_t)t * ks * kFrag + 8 * lane;
         if (16 * t < mlp_pad(N)) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
+            for (int k = 0; k < KS; ++k)
                 if (k < ks) b[k] = *reinterpret_cast<const bf16x8 *>(P + k * kFrag);
         }
         bias = (fwd && c < N) ? net.wt[net.woff[l] + K * N + c] : 0.0f;
@@ -417,7 +423,7 @@ __global__ void __launch_bounds__(64 * NW)
             if (m + i >= rows) v[i] = (bf16)0.0f;
         *reinterpret_cast<bf16x4 *>(P + frag_index(c, (int)(r0 + m), net.steps)) = v;
     };
-    bf16x8 b[4];
+    bf16x8 b[KS];
     float bias;
     fetch(0, wave, b, bias);
     const int w0 = net.w[0], w0p = mlp_pad(w0);
@@ -447,7 +453,7 @@ __global__ void __launch_bounds__(64 * NW)
             if (t != wave) fetch(l, t, b, bias);
 #pragma unroll 1
             for (int mb = 0; mb < MB; ++mb) {
-                const f32x4 acc = block_product(in + 16 * mb * kLd, b, ks, lane);
+                const f32x4 acc = block_product<W>(in + 16 * mb * kLd, b, ks, lane);
                 const int m = 16 * mb + mq;
                 bf16x4 h;
 #pragma unroll
@@ -487,7 +493,7 @@ __global__ void __launch_bounds__(64 * NW)
             if (t != wave) fetch(step, t, b, bias);
 #pragma unroll 1
             for (int mb = 0; mb < MB; ++mb) {
-                const f32x4 acc = block_product(in + 16 * mb * kLd, b, ks, lane);
+                const f32x4 acc = block_product<W>(in + 16 * mb * kLd, b, ks, lane);
                 const int m = 16 * mb + mq;
                 bf16x4 h;
 #pragma unroll
@@ -677,7 +683,13 @@ void batch_slices(int64_t n, int &nsl, int &kslice) {
     nsl = (int)((n + kslice - 1) / kslice);
 }
 
-size_t rows_lds(int mb, int bufs) { return (size_t)bufs * 16 * mb * kLd * sizeof(bf16); }
+size_t rows_lds(int W, int mb, int bufs) {
+    return (size_t)bufs * 16 * mb * lds_row(W) * sizeof(bf16);
+}
+
+bool wide(const MlpNet &net) {
+    return std::any_of(net.w, net.w + net.L + 1, [](int w) { return w > 128; });
+}
 
 }  // namespace
 
@@ -696,31 +708,46 @@ int64_t mlp_loss_parts(int64_t n) { return (n + 31) / 32 * 2; }
 // rows 361 and 382); up to 32,768 rows tiles of 16 spread wider (20,000: 18.8
 // against 22.1 us), and up to 8,192, where a call is one chain of layers, a
 // wavefront per 16-column block shortens each (4,000: 8.0, with four
-// wavefronts 11.6, tiles of 32 18.2).
+// wavefronts 11.6, tiles of 32 18.2).  Wider than 128 a layer has twice the
+// blocks and eight wavefronts are better throughout (6-256x3-4, the call: 400,000
+// rows 378 us with tiles of 32, 601 with 16, 417 with four wavefronts; 2,000 rows
+// 32.4 with tiles of 32, 26.1 with 16; layer by layer 2155 and 43.1).
 hipError_t launch_mlp_forward(hipStream_t st, const MlpNet &net, const float *X, float *Y,
                               int64_t n) {
     if (n <= 0) return hipSuccess;
+    const int W = wide(net) ? 256 : 128;
     auto go = [&](auto kern, int mb, int nw) {
         const int64_t wgs = (n + 16 * mb - 1) / (16 * mb);
-        hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * nw), rows_lds(mb, 2), st, net, n, X,
-                           (const float *)nullptr, Y, 0.0f, (float *)nullptr);
+        hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * nw), rows_lds(W, mb, 2), st, net, n,
+                           X, (const float *)nullptr, Y, 0.0f, (float *)nullptr);
         return hipGetLastError();
     };
-    if (n <= 8192) return go(k_mlp_rows<1, 8, false>, 1, 8);
-    if (n <= 32768) return go(k_mlp_rows<1, 4, false>, 1, 4);
-    return go(k_mlp_rows<2, 4, false>, 2, 4);
+    if (W == 256) {
+        if (n <= 8192) return go(k_mlp_rows<256, 1, 8, false>, 1, 8);
+        return go(k_mlp_rows<256, 2, 8, false>, 2, 8);
+    }
+    if (n <= 8192) return go(k_mlp_rows<128, 1, 8, false>, 1, 8);
+    if (n <= 32768) return go(k_mlp_rows<128, 1, 4, false>, 1, 4);
+    return go(k_mlp_rows<128, 2, 4, false>, 2, 4);
 }
 
 // 16 rows per workgroup and a wavefront per 16-column block: the row kernel is
 // a chain of layers, and 8,192 rows then put two workgroups on each CU (23 us;
-// 32 rows and eight wavefronts 31, four 44).
+// 32 rows and eight wavefronts 31, four 44).  Wider than 128 a wavefront takes two
+// blocks (6-256x3-4, 8,192 rows, the call: 122 us, with sixteen wavefronts 130,
+// layer by layer 318).
 hipError_t launch_mlp_gradient(hipStream_t st, const MlpNet &net, const float *X, const float *T,
                                int64_t n, float *part, float *losspart, float *loss,
                                const MlpAdam *adam) {
     const int nloss = (int)mlp_loss_parts(n);
     const float scale = (float)(2.0 / (double)(n * net.w[net.L]));
-    hipLaunchKernelGGL((k_mlp_rows<1, 8, true>), dim3(nloss), dim3(64 * 8), rows_lds(1, net.L + 2),
-                       st, net, n, X, T, (float *)nullptr, scale, losspart);
+    const int W = wide(net) ? 256 : 128;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(nloss), dim3(64 * 8), rows_lds(W, 1, net.L + 2), st, net, n,
+                           X, T, (float *)nullptr, scale, losspart);
+    };
+    if (W == 256) go(k_mlp_rows<256, 1, 8, true>);
+    else go(k_mlp_rows<128, 1, 8, true>);
     int nsl, kslice, nblock = 0, cols = 0;
     batch_slices(n, nsl, kslice);
     for (int l = 0; l < net.L; ++l) {

@@ -39,9 +39,10 @@ hipError_t launch_weights_bf16(hipStream_t st, int fi, int fo, const float *W, b
 
 // --- networks that fit the fused path ---------------------------------------
 // Every width at most kFuseWidth and at most kFuseLayers layers: a workgroup
-// then holds the activations of its rows in LDS through all layers.  Wider
-// layers would leave one workgroup per CU and are served by the products above.
-constexpr int kFuseWidth = 128, kFuseLayers = 6;
+// then holds the activations of its rows in LDS through all layers (68 KB to
+// train the widest, two workgroups per CU).  Wider layers would leave one
+// workgroup per CU and are served by the products above.
+constexpr int kFuseWidth = 256, kFuseLayers = 6;
 
 // One network and its training workspace as the fused kernels see it.  The
 // matrix-core operands lie in memory as the instruction takes them, in

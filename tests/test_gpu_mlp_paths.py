@@ -1,5 +1,5 @@
-"""The network's two paths at their edges: the fused one (widths up to 128, up to
-six layers) and, past either limit, layer by layer.
+"""The network's paths at their edges: the fused one (widths up to 128 and up to
+256, up to six layers) and, past either limit, layer by layer.
 
 With small integers every bfloat16 operand and FP32 sum is exact, so a linear
 layer of either path equals FP64 bit for bit.  Deep networks are held to the
@@ -32,7 +32,8 @@ def _rel(a, b):
     return float(np.max(np.abs(np.asarray(a, np.float64) - b)) / max(np.max(np.abs(b)), 1e-30))
 
 
-@pytest.mark.parametrize("K,N", [(1, 1), (17, 33), (128, 127), (129, 3), (40, 200)])
+@pytest.mark.parametrize("K,N", [(1, 1), (17, 33), (128, 127), (129, 3), (40, 200),
+                                 (256, 256), (255, 131), (257, 3), (33, 300)])
 def test_linear_rows_exact(env, K, N):
     torch, ql = env
     rng = np.random.default_rng(K + 7 * N)
@@ -56,7 +57,8 @@ def test_linear_rows_exact(env, K, N):
 
 
 @pytest.mark.parametrize("widths", [[2, 5, 1], [6, 17, 33, 4], [3, 16, 16, 16, 16, 16, 2],
-                                    [128, 128, 128], [3, 16, 16, 16, 16, 16, 16, 2], [6, 130, 4]])
+                                    [128, 128, 128], [3, 16, 16, 16, 16, 16, 16, 2], [6, 130, 4],
+                                    [6, 256, 129, 4], [256, 200, 256], [2, 300, 1]])
 def test_deep_paths_match_emulator(env, widths):
     torch, ql = env
     rng = np.random.default_rng(len(widths))
