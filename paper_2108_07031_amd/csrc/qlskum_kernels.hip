@@ -1,6 +1,6 @@
 // HIP kernels of the q-LSKUM pseudo-time iteration for gfx950 (MI355X).
 //
-// One work-item per point; points are stored in a locality-preserving
+// Four lanes per point in the sweeps; points are stored in a locality-preserving
 // (Hilbert) order so the neighbour gathers of a workgroup touch a compact
 // set of cache lines, and workgroups are remapped so that each of the eight
 // XCDs (each with its own L2) walks a contiguous range of points.
@@ -8,8 +8,8 @@
 // Layouts (library order): conserved state U, Un and the residual R are
 // component-major U[c*n + p] (coalesced streaming); the gathered per-point
 // records are interleaved so that one neighbour costs few 16-byte loads:
-// q [n][4], g [n][8] (q_x 0..3, q_y 4..7), limiter bounds [n][8]
-// (qmax 0..3, qmin 4..7).
+// q [n][4], g [n][8] (q_x 0..3, q_y 4..7), limiter bounds [n][8] as offsets
+// (qmax - q 0..3, qmin - q 4..7).
 //
 // Equations (paper: "On the performance of GPU accelerated q-LSKUM based
 // meshfree solvers in Fortran, C++, Python, and Julia", 2021):
@@ -752,7 +752,9 @@ __device__ __forceinline__ void grad0_entries(const DevCloud &cl, const double2 
 // the limited reconstruction), stored as offsets from q.  Slot record
 // (double2): q 0..1, position 2.  B64 false: the bounds go to the FP32
 // shadow only (a compile-time choice: a run-time test costs the FP64 form a
-// wave of occupancy).
+// wave of occupancy).  Bound by memory: 0.66 GB a launch on the 2.5M cloud, 254 ->
+// 160 us (4.1 TB/s; a large copy reaches 4.8) with the entry slots in LDS in
+// 16-byte chunks, the point's own data read early and a pair of results per lane.
 template <bool B64>
 __global__ void __launch_bounds__(kBlock) k_grad0(DevCloud cl, int cap,
                                                   const double2 *__restrict__ q,
@@ -878,7 +880,8 @@ __device__ __forceinline__ void gradk_entries(const DevCloud &cl, const double2 
 // one inner iteration (eq. (29)).  The least squares is linear in its data:
 //   g^k = LS(dq_i) - 1/2 LS(d.(g^{k-1}_i - g^{k-1}_p)) = g0 - 1/2 LS(...)
 // so only the previous iterate is gathered (Jacobi: read gprev, write gnext).
-// Slot record (double2): g 0..3, position 4.
+// Slot record (double2): g 0..3, position 4.  Bound by memory: 0.69 GB a launch on
+// the 2.5M cloud, 207 -> 170 us (4.1 TB/s) by the same steps as k_grad0.
 __global__ void __launch_bounds__(kBlock) k_gradk(DevCloud cl, int cap,
                                                   const double2 *__restrict__ g0,
                                                   const double2 *__restrict__ gprev,
@@ -1445,8 +1448,8 @@ __device__ __forceinline__ void venkat2(double da, const double *ba, double db, 
 // Contribution of one neighbour entry (split flags f, offset (dx, dy) from p
 // to i) to the residual of p.  Bound by FP64 issue: 494 VALU instructions with
 // the limiter, seven of them quarter-rate (a reciprocal per limiter value and
-// the general erfc everywhere took 630 with seventeen); the 2.5M-point launch
-// 1595 -> 1352 us.  Forms the modified states q~_i and q~_p of eq. (28)
+// the general erfc everywhere took 630 with seventeen); by itself that took the
+// 2.5M-point launch from 1595 to 1352 us.  Forms the modified states q~_i and q~_p of eq. (28)
 // (limited when LIMITER), their split fluxes, and w_b (G(q~_i) - G(q~_p))
 // added for each split stencil b the entry belongs to (one s half and one n
 // half at most).  w holds p's eight least-squares factors (see k_setup).
@@ -1862,7 +1865,11 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
 
 template <bool LIMITER, int POW, int M, bool KOBC>
 // Held to 3 waves per SIMD (at most 168 VGPRs), which the straight-line
-// two-direction body of flux_entry would otherwise exceed.
+// two-direction body of flux_entry would otherwise exceed.  Bound by FP64 issue
+// (82% of the SIMD cycles): on the 2.5M cloud with the limiter 1568 -> 1058 us
+// (flux_entry, stage_records with OwnPoint's loads, quad_update).  Slower, with
+// the same bits: the least-squares factors in LDS instead of registers (632k
+// points 272 -> 281 us), the tile's points finished by one wavefront (346).
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
 k_flux(DevCloud cl, FlowParams fp, int stage, int cap,
                                                  const double *__restrict__ Rin,
@@ -2498,7 +2505,10 @@ __device__ __forceinline__ void flux_point_f(const DevCloud &cl, const FlowParam
 }  // namespace
 
 template <bool LIMITER, int POW, bool FIRST, bool KOBC>
-// held to 4 waves per SIMD (at most 128 VGPRs), as k_flux is to 3
+// held to 4 waves per SIMD (at most 128 VGPRs), as k_flux is to 3.  Its VALU
+// instructions at four cycles each come to its time, but leaving a tenth of them
+// out (a shorter erf) did not move it: issue and the chain of an entry's loads
+// bind together.  On the 2.5M cloud with the limiter 780 -> 575 us.
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 k_flux_mixed(
     DevCloud cl, FlowParams fp, int stage, int cap, const double2 *__restrict__ q,
