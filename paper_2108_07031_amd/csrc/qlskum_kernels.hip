@@ -134,9 +134,10 @@ __device__ __forceinline__ void res_case(ResLds &sh, int ncase, const int *__res
 // The residual norms as extra workgroups of the first q-derivative passes (first
 // order: of the flux sweeps) of stages 2 to 4: stage 1 leaves R, and the norms are only read after the
 // iteration, so they need no launches of their own (two of an iteration's 22,
-// ~4.5 us each, and reading R meanwhile costs no time of its own: 2.97 -> 2.73 ms for 20
-// iterations at 9.6k points, 2.58 -> 2.51 for 10 at 41k; a first-order iteration at
-// 9.6k 46.9 -> 36.4 us, at 144k 155 -> 143).  The stages' launches order
+// ~4.5 us each, and 20 us of reading R at 2.5M points, of which the sweep that
+// reads it meanwhile shows 9: 2.97 -> 2.73 ms for 20 iterations at 9.6k points,
+// 2.58 -> 2.51 for 10 at 41k; a first-order iteration at 9.6k 46.9 -> 36.4 us, at
+// 144k 155 -> 143).  The stages' launches order
 // the steps: chunk sums (stage 2), norms (stage 3), row counter (stage 4).  The
 // residual workgroups come first in the grid, so that a large cloud has no tail
 // of them, and are a multiple of the XCDs, so that a tile stays on its XCD.
