@@ -329,7 +329,11 @@ int ql_mlp_set_weights(ql_mlp *m, const float *w);
 int ql_mlp_get_weights(ql_mlp *m, float *w);
 
 /* Y[n][w_out] = network(X[n][w_in]); X, Y device FP32, row-major, enqueued
- * on the network's stream.  Errors: QL_EINVAL, QL_ESTATE (no weights). */
+ * on the network's stream.  n may exceed max_batch.  Y may overlap X: the rows
+ * are then taken max_batch at a time, each chunk read whole before its outputs
+ * are written, so that up to max_batch rows every overlap works, and more rows
+ * work where no chunk's outputs reach the rows of a later one (w_out <= w_in with
+ * both from the same address).  Errors: QL_EINVAL, QL_ESTATE (no weights). */
 int ql_mlp_forward(ql_mlp *m, const float *X, float *Y, int64_t n);
 
 /* Mean squared error over the n x w_out outputs of one batch (device X, T;

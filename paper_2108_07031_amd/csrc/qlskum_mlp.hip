@@ -390,9 +390,10 @@ __device__ __forceinline__ f32x4 block_product(const bf16 *A, const bf16x8 b[W /
 // the first (each row's own).  a_l and d_l are left in memory as fragments along
 // the batch, zero past row n: a lane's four results are consecutive rows of one
 // column, and the wavefront's 8-byte stores fill 512 bytes in a row.
-template <int W, int MB, int NW, bool TRAIN>
+// XT: float, or bf16 for rows that were converted before (outputs over X).
+template <int W, int MB, int NW, bool TRAIN, class XT = float>
 __global__ void __launch_bounds__(64 * NW)
-    k_mlp_rows(MlpNet net, int64_t n, const float *__restrict__ X, const float *__restrict__ T,
+    k_mlp_rows(MlpNet net, int64_t n, const XT *__restrict__ X, const float *__restrict__ T,
                float *__restrict__ Y, float scale, float *__restrict__ losspart) {
     constexpr int MT = 16 * MB, kLd = lds_row(W), KS = W / 32;
     extern __shared__ __align__(16) bf16 sm[];
@@ -729,6 +730,17 @@ hipError_t launch_mlp_forward(hipStream_t st, const MlpNet &net, const float *X,
     if (n <= 8192) return go(k_mlp_rows<128, 1, 8, false>, 1, 8);
     if (n <= 32768) return go(k_mlp_rows<128, 1, 4, false>, 1, 4);
     return go(k_mlp_rows<128, 2, 4, false>, 2, 4);
+}
+
+// One tile form for every width and row count: a rare call, which has paid a pass
+// over X for its copy.
+hipError_t launch_mlp_forward_bf16(hipStream_t st, const MlpNet &net, const bf16 *X, float *Y,
+                                   int64_t n) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL((k_mlp_rows<256, 2, 8, false, bf16>), dim3((unsigned)((n + 31) / 32)),
+                       dim3(64 * 8), rows_lds(256, 2, 2), st, net, n, X, (const float *)nullptr, Y,
+                       0.0f, (float *)nullptr);
+    return hipGetLastError();
 }
 
 // 16 rows per workgroup and a wavefront per 16-column block: the row kernel is

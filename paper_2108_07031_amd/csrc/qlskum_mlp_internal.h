@@ -64,9 +64,12 @@ bool mlp_fusable(const int *widths, int nwidth);
 size_t mlp_part_floats(int np, int64_t n);
 // loss partials of a gradient of n rows
 int64_t mlp_loss_parts(int64_t n);
-// Y = network(X), n rows
+// Y = network(X), n rows; Y may not overlap X (row tiles run in any order)
 hipError_t launch_mlp_forward(hipStream_t st, const MlpNet &net, const float *X, float *Y,
                               int64_t n);
+// the same for at most 2^26 rows already rounded to bf16 (row-major [n][w_in])
+hipError_t launch_mlp_forward_bf16(hipStream_t st, const MlpNet &net, const bf16 *X, float *Y,
+                                   int64_t n);
 // gradient of the mean squared error over n rows into net.g and the sum of
 // squared errors into *loss; with adam, one Adam step on net.wt, m and v and the
 // bf16 copies of the new weights

@@ -212,6 +212,12 @@ bool alloc_layers(ql_mlp *m, int maxw) {
     return ok && (gp == 0 || malloc_n(&m->gpart, gp) == hipSuccess);
 }
 
+// the byte ranges [a, a + na) and [b, b + nb) share memory
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + nb && y < x + na;
+}
+
 int check_batch(ql_mlp *m, const void *X, const void *T, int64_t n, bool need_t) {
     if (!X || (need_t && !T)) return mfail(m, QL_EINVAL, "null device pointer");
     if (n < 1 || n > m->max_batch)
@@ -328,12 +334,20 @@ int ql_mlp_forward(ql_mlp *m, const float *X, float *Y, int64_t n) {
     if (st) return st;
     if (n < 0 || (n > 0 && (!X || !Y))) return mfail(m, QL_EINVAL, "bad forward arguments");
     const int w0 = m->widths.front(), wL = m->widths.back();
-    if (m->net.L) {
+    const bool fused = m->net.L > 0;
+    if (fused && !overlap(X, sizeof(float) * n * w0, Y, sizeof(float) * n * wL)) {
         MCHK(m, launch_mlp_forward(m->stream, m->net, X, Y, n));
         return QL_OK;
     }
+    // Outputs over the inputs: every chunk is converted before its outputs are
+    // written, since the fused kernel's row tiles read X and write Y in any order.
     for (int64_t r = 0; r < n; r += m->max_batch) {
         const int64_t b = std::min(m->max_batch, n - r);
+        if (fused) {
+            MCHK(m, launch_to_bf16(m->stream, b, w0, w0, X + r * w0, m->act[0]));
+            MCHK(m, launch_mlp_forward_bf16(m->stream, m->net, m->act[0], Y + r * wL, b));
+            continue;
+        }
         if ((st = forward(m, X + r * w0, b))) return st;
         MCHK(m, hipMemcpyAsync(Y + r * wL, m->y, sizeof(float) * b * wL,
                                hipMemcpyDeviceToDevice, m->stream));
