@@ -217,6 +217,11 @@ __global__ void __launch_bounds__(256) k_to_bf16(int64_t n, int w, int ld,
 hipError_t launch_to_bf16(hipStream_t st, int64_t n, int w, int ld, const float *x, bf16 *y) {
     const int64_t tot = n * ld;
     if (tot == 0) return hipSuccess;
+    if (tot >= (int64_t)1 << 32) {  // more threads than one launch holds
+        const hipError_t e = launch_to_bf16(st, n / 2, w, ld, x, y);
+        return e != hipSuccess ? e
+                               : launch_to_bf16(st, n - n / 2, w, ld, x + n / 2 * w, y + n / 2 * ld);
+    }
     hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, n, w, ld,
                        x, y);
     return hipGetLastError();
@@ -713,8 +718,18 @@ int64_t mlp_loss_parts(int64_t n) { return (n + 31) / 32 * 2; }
 // blocks and eight wavefronts are better throughout (6-256x3-4, the call: 400,000
 // rows 378 us with tiles of 32, 601 with 16, 417 with four wavefronts; 2,000 rows
 // 32.4 with tiles of 32, 26.1 with 16; layer by layer 2155 and 43.1).
+//
+// A launch holds fewer than 2^32 threads and a grid past that is cut without an
+// error, so more rows (16 threads each in the wide form) go in several launches.
 hipError_t launch_mlp_forward(hipStream_t st, const MlpNet &net, const float *X, float *Y,
                               int64_t n) {
+    constexpr int64_t kMaxRows = (int64_t)1 << 27;
+    for (; n > kMaxRows; n -= kMaxRows) {
+        const hipError_t e = launch_mlp_forward(st, net, X, Y, kMaxRows);
+        if (e != hipSuccess) return e;
+        X += kMaxRows * net.w[0];
+        Y += kMaxRows * net.w[net.L];
+    }
     if (n <= 0) return hipSuccess;
     const int W = wide(net) ? 256 : 128;
     auto go = [&](auto kern, int mb, int nw) {
