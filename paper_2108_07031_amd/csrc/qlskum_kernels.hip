@@ -1421,7 +1421,10 @@ __device__ __forceinline__ void split_flux(const Prim &s, double ex, double ey, 
 // and dmin.  The denominator is (D + delta/2)^2 + 7/4 delta^2 + eps^2 >=
 // eps^2 > 0: callers keep eps^2 at least kEps2Min, so that coincident points
 // (D = delta = eps = 0, the one 0/0 case) give phi = 1 without a test here.
-constexpr double kEps2Min = 1e-150;  // its square is still a normal number
+// Their products in venkat2 need its square to be a normal number.  It can change
+// a reconstructed value by no more than an increment |delta| below about 1e-75, where
+// delta^2 and D^2 are no longer large against it.
+constexpr double kEps2Min = 1e-150;
 __device__ __forceinline__ double venkat(double delta, double dmax, double dmin, double eps2) {
 #pragma clang fp contract(off)
     const double D = (delta > 0.0) ? dmax : dmin;
@@ -1432,10 +1435,20 @@ __device__ __forceinline__ double venkat(double delta, double dmax, double dmin,
 }
 
 // Two limiter values with one reciprocal, 1/a = b/(ab): the reciprocal costs
-// as much as seven other operations here, the three products three.
+// as much as seven other operations here, the three products three.  The product
+// overflows where both denominators lie past about 1e154 (K |P_i - P| past 2e51, or
+// differences of q past 1e77); the values are then NaN, the modified states have no
+// Maxwellian, and the point is summed again with WIDE, one reciprocal each.  The
+// product cannot underflow (kEps2Min).
+template <bool WIDE>
 __device__ __forceinline__ void venkat2(double da, const double *ba, double db, const double *bb,
                                         double eps2, double &pa, double &pb) {
 #pragma clang fp contract(off)
+    if constexpr (WIDE) {
+        pa = venkat(da, ba[0], ba[4], eps2);
+        pb = venkat(db, bb[0], bb[4], eps2);
+        return;
+    }
     const double Da = (da > 0.0) ? ba[0] : ba[4], Db = (db > 0.0) ? bb[0] : bb[4];
     const double a2 = fma(Da, Da, eps2), b2 = fma(Db, Db, eps2);
     const double na = fma(2.0 * da, Da, a2), nb = fma(2.0 * db, Db, b2);
@@ -1460,7 +1473,8 @@ __device__ __forceinline__ void venkat2(double da, const double *ba, double db, 
 // Maxwellian.
 // M: the split stencils evaluated (Split bits; 15 all four).  The caller
 // masks f with M, so a direction is evaluated when M holds either half.
-template <bool LIMITER, int POW, int M = 15>
+// WIDE: see venkat2.
+template <bool LIMITER, int POW, int M, bool WIDE>
 __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, double2 N,
                                            const double qi[4], const double gi[8],
                                            const double bi[8], const double qp[4],
@@ -1483,7 +1497,7 @@ __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, doub
             const double di = fma(hx, gi[r], hy * gi[4 + r]);
             const double d0 = fma(hx, gp[r], hy * gp[4 + r]);
             double pi, p0;
-            venkat2(di, bi + r, d0, bp + r, eps2, pi, p0);
+            venkat2<WIDE>(di, bi + r, d0, bp + r, eps2, pi, p0);
             qti[r] = fma(pi, di, qi[r]);
             qt0[r] = fma(p0, d0, qp[r]);
         }
@@ -1774,12 +1788,13 @@ __device__ __forceinline__ void stage_records(const DevCloud &cl, double2 *lds, 
 // Residual sums of live point p (slot j of its tile) over its entries
 // o.k, o.k + kFluxLanes, ...; IN_LDS: the records come from the tile's LDS
 // image, else from memory (one instantiation each, so that no load is
-// generic).  Reports a failed reconstruction.
-template <bool IN_LDS, bool LIMITER, int POW, int M, bool KOBC>
-__device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams &fp,
+// generic).  WIDE: see venkat2.  Returns false when a modified state has no
+// Maxwellian.
+template <bool IN_LDS, bool LIMITER, int POW, int M, bool KOBC, bool WIDE = false>
+__device__ __forceinline__ bool flux_point(const DevCloud &cl, const FlowParams &fp,
                                            const double2 *lds, int j, int p, const OwnPoint &o,
                                            const double2 *q, const double2 *g,
-                                           const double2 *qmm, double R[4], ErrWord *err) {
+                                           const double2 *qmm, double R[4]) {
     constexpr int kRec = LIMITER ? 11 : 7;
     double qp[4], gp[8], bp[8];
     if constexpr (IN_LDS) {
@@ -1843,8 +1858,8 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
             if (LIMITER) load8(qmm, i, bi);
             Q = cl.xy[i];
         }
-        ok &= flux_entry<LIMITER, POW, M>(f, Q.x - o.P.x, Q.y - o.P.y, o.N, qi, gi, bi, qp,
-                                                 gp, bp, o.w, fp, R);
+        ok &= flux_entry<LIMITER, POW, M, WIDE>(f, Q.x - o.P.x, Q.y - o.P.y, o.N, qi, gi, bi, qp,
+                                                gp, bp, o.w, fp, R);
     }
     if constexpr (KOBC && (M & kNMinus)) {
         if (o.kd == kOuter) {
@@ -1859,7 +1874,25 @@ __device__ __forceinline__ void flux_point(const DevCloud &cl, const FlowParams 
             }
         }
     }
-    if (!ok) report_pt(cl, err, p, kErrPositivity);
+    return ok;
+}
+
+// The sums of a point of k_flux that failed, from memory and with one reciprocal
+// per limiter value.  Everything is read again through an index that the compiler
+// cannot relate to p, so that the sweep holds no register for this rare path (kept in
+// registers, it slowed the launch by 3%; read again, by 1%: 1054 -> 1065 us at 2.5M
+// points.  A reciprocal per limiter value in the sweep itself would take 16 more of
+// its 494 instructions per entry).
+template <int POW, int M, bool KOBC>
+__device__ __forceinline__ bool flux_point_wide(const DevCloud &cl, const FlowParams &fp, int p,
+                                                int sub, const double2 *q, const double2 *g,
+                                                const double2 *qmm, double R[4]) {
+    asm volatile("" : "+v"(p));
+    OwnPoint o;
+    o.load(cl, p, sub);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) R[r] = 0.0;
+    return flux_point<false, true, POW, M, KOBC, true>(cl, fp, nullptr, 0, p, o, q, g, qmm, R);
 }
 
 }  // namespace
@@ -1917,11 +1950,12 @@ k_flux(DevCloud cl, FlowParams fp, int stage, int cap,
     }
     const double2 N = o.N;
     if (live) {
-        if (in_lds)
-            flux_point<true, LIMITER, POW, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R, err);
-        else
-            flux_point<false, LIMITER, POW, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R,
-                                                            err);
+        bool ok = in_lds ? flux_point<true, LIMITER, POW, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R)
+                         : flux_point<false, LIMITER, POW, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R);
+        if constexpr (LIMITER) {
+            if (!ok) ok = flux_point_wide<POW, M, KOBC>(cl, fp, p, sub, q, g, qmm, R);
+        }
+        if (!ok) report_pt(cl, err, p, kErrPositivity);
     }
     double Rs = lane_group_sum4(R, sub);
     if (j >= nown) return;
