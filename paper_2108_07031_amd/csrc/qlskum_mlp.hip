@@ -365,6 +365,27 @@ __device__ __forceinline__ size_t frag_index(int c, int k, int steps) {
            (k & 7);
 }
 
+// Element (column c, row k) of a batch array of w columns: fragments along the
+// rows, the columns past the last whole 16 in fragments of their own number of
+// columns (a narrow layer then takes its own size, where whole fragments took up to
+// 16 times that).
+__device__ __forceinline__ size_t batch_index(int c, int k, int w, int steps) {
+    return (size_t)(c >> 4) * steps * kFrag + (size_t)(k >> 3) * (8 * min(16, w - (c & ~15))) +
+           8 * (c & 15) + (k & 7);
+}
+// A lane's eight rows of step 0 in 16-column block j of such an array, and the
+// distance between steps.  Lanes past the block's columns read its last one; what
+// they make of it is not stored.
+struct BatchLane {
+    const bf16 *p;
+    int step;
+    __device__ __forceinline__ BatchLane(const bf16 *P, int j, int w, int steps, int c, int quarter) {
+        const int wb = min(16, w - 16 * j);
+        p = P + (size_t)j * steps * kFrag + 8 * (quarter * wb + min(c, wb - 1));
+        step = 32 * wb;
+    }
+};
+
 // 16 x 16 block: rows of A in LDS (leading dimension lds_row(W), zero past K),
 // columns b of B, K in ks steps of 32
 template <int W>
@@ -392,8 +413,8 @@ __device__ __forceinline__ f32x4 block_product(const bf16 *A, const bf16x8 b[W /
 // W: the widths' limit, 128 or 256 (a narrow network would hold the wider form's
 // operand registers and LDS rows without using them).
 // TRAIN: the same, then the output error and the errors of every layer back to
-// the first (each row's own).  a_l and d_l are left in memory as fragments along
-// the batch, zero past row n: a lane's four results are consecutive rows of one
+// the first (each row's own).  a_l and d_l are left in memory as batch arrays
+// (batch_index), zero past row n: a lane's four results are consecutive rows of one
 // column, and the wavefront's 8-byte stores fill 512 bytes in a row.
 // XT: float, or bf16 for rows that were converted before (outputs over X).
 template <int W, int MB, int NW, bool TRAIN, class XT = float>
@@ -422,12 +443,13 @@ __global__ void __launch_bounds__(64 * NW)
         }
         bias = (fwd && c < N) ? net.wt[net.woff[l] + K * N + c] : 0.0f;
     };
-    // rows m .. m + 3 of column c into a batch fragment array, zero past row n
-    auto put = [&](bf16 *P, int m, int c, bf16x4 v) {
+    // rows m .. m + 3 of column c into a batch array of w columns, zero past row n
+    auto put = [&](bf16 *P, int m, int c, int w, bf16x4 v) {
+        if (c >= w) return;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (m + i >= rows) v[i] = (bf16)0.0f;
-        *reinterpret_cast<bf16x4 *>(P + frag_index(c, (int)(r0 + m), net.steps)) = v;
+        *reinterpret_cast<bf16x4 *>(P + batch_index(c, (int)(r0 + m), w, net.steps)) = v;
     };
     bf16x8 b[KS];
     float bias;
@@ -444,7 +466,7 @@ __global__ void __launch_bounds__(64 * NW)
             bf16x4 v;
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = buf(0)[(m + i) * kLd + c];
-            put(net.aT[0], m, c, v);
+            put(net.aT[0], m, c, w0, v);
         }
     }
     float e2 = 0.0f;
@@ -479,7 +501,7 @@ __global__ void __launch_bounds__(64 * NW)
                 if (last && !TRAIN) continue;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) out[(m + i) * kLd + c] = h[i];
-                if (TRAIN) put(last ? net.dT[l] : net.aT[l + 1], m, c, h);
+                if (TRAIN) put(last ? net.dT[l] : net.aT[l + 1], m, c, fo, h);
             }
         }
         if (!last || (TRAIN && net.L > 1)) fetch(l + 1, wave, b, bias);
@@ -508,7 +530,7 @@ __global__ void __launch_bounds__(64 * NW)
                     h[i] = c < fi ? (bf16)(acc[i] * (1.0f - av * av)) : (bf16)0.0f;
                     out[(m + i) * kLd + c] = h[i];
                 }
-                put(net.dT[l - 1], m, c, h);
+                put(net.dT[l - 1], m, c, fi, h);
             }
         }
         if (l > 1) fetch(step + 1, wave, b, bias);
@@ -527,39 +549,64 @@ __global__ void __launch_bounds__(64 * NW)
 
 // All layers' weight gradients a_{l-1}^T d_l in one launch: wavefront (slice,
 // block) sums one 16 x 32 block over its slice of the rows into
-// part[slice][flat weight].  The workgroups past the blocks sum the bias
-// gradients of 16 columns of d_l each, in k_colsum's order: row r belongs to
-// partial sum r % 256, a thread holds eight consecutive ones of a column (one
-// 16-byte load a round) for two row groups, and the 256 are added as a tree.
-// 8,192 rows of the 6-128x4-4 network 14.4 us; one launch per layer and sum,
+// part[slice][flat weight].  The first workgroups sum the bias gradients of 16
+// columns of d_l each, in k_colsum's order: row r belongs to partial sum r % 256, a
+// thread holds eight consecutive ones of a column (one 16-byte load a round) for two
+// row groups, and the 256 are added as a tree.  They are the longest chains, so they
+// start first (last in the grid: 15.1 us where this is 12.8).  Bound by load latency:
+// a chain's loads are issued in batches, held in that order by scheduling barriers
+// (without them 19.3 us), with four waves per SIMD as the registers' target.
+// 8,192 rows of the 6-128x4-4 network 12.8 us; one launch per layer and sum,
 // gathering both operands two bytes at a time, took 105.
-__global__ void __launch_bounds__(64 * kWaves)
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4, 4)))
     k_mlp_wgrad(MlpNet net, int n, int kslice, int nblock, int items, float *__restrict__ part) {
-    const int gemm_wgs = (items + kWaves - 1) / kWaves;
+    const int bias_wgs = gridDim.x - (items + kWaves - 1) / kWaves;
     const int lane = threadIdx.x & 63;
-    if ((int)blockIdx.x >= gemm_wgs) {
+    if ((int)blockIdx.x < bias_wgs) {
         __shared__ float red[256][17];
-        int j = blockIdx.x - gemm_wgs, l = 0;
+        int j = blockIdx.x, l = 0;
         while (j >= (net.w[l + 1] + 15) / 16) j -= (net.w[++l] + 15) / 16;
         const int steps = (n + 31) / 32;
-        const bf16 *d = net.dT[l] + (size_t)j * net.steps * kFrag;
         // rows 8 g .. 8 g + 7 (mod 256) of column c; g and g + 16
         const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
+        const BatchLane d(net.dT[l], j, net.w[l + 1], net.steps, c, g & 3);
         float s[2][8] = {};
-        auto add = [&](int st, float t[8]) {
-            const bf16x8 v = *reinterpret_cast<const bf16x8 *>(
-                d + (size_t)st * kFrag + ((g & 3) * 16 + c) * 8);
+        auto add = [](bf16x8 v, float t[8]) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) t[i] += (float)v[i];
         };
-        int k = g >> 2;  // whole rounds of 256 rows without a test, so that loads overlap
-#pragma unroll 8
-        for (; k + 8 - (g >> 2) <= steps; k += 8) {
-            add(k, s[0]);
-            add(k + 4, s[1]);
-        }
-        if (k < steps) add(k, s[0]);
-        if (k + 4 < steps) add(k + 4, s[1]);
+        // whole rounds of 256 rows, kBatch at a time with all their loads in flight
+        constexpr int kBatch = 8;
+        auto sum = [&](int step) {
+            const bf16 *q = d.p + (size_t)(g >> 2) * step;
+            auto load = [&](int at) {
+                return *reinterpret_cast<const bf16x8 *>(q + (size_t)at * step);
+            };
+            const int left = steps % 8 - (g >> 2);
+            int r = steps / 8;
+            for (; r >= kBatch; r -= kBatch, q += 8 * kBatch * (size_t)step) {
+                bf16x8 v[2 * kBatch];
+#pragma unroll
+                for (int u = 0; u < 2 * kBatch; ++u) {
+                    v[u] = load(4 * u);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int u = 0; u < 2 * kBatch; ++u) {
+                    add(v[u], s[u & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            for (; r > 0; --r, q += 8 * (size_t)step) {
+                add(load(0), s[0]);
+                add(load(4), s[1]);
+            }
+            if (left > 0) add(load(0), s[0]);
+            if (left > 4) add(load(4), s[1]);
+        };
+        // whole blocks lie at constant distances, which take no address registers
+        if (d.step == kFrag) sum(kFrag);
+        else sum(d.step);
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -573,7 +620,7 @@ __global__ void __launch_bounds__(64 * kWaves)
             net.g[net.woff[l] + net.w[l] * net.w[l + 1] + 16 * j + c] = red[0][c];
         return;
     }
-    const int item = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    const int item = (blockIdx.x - bias_wgs) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (item >= items) return;  // whole wavefront leaves together
     const int sl = item / nblock;
     int blk = item - sl * nblock, l = 0, ntn;
@@ -586,19 +633,37 @@ __global__ void __launch_bounds__(64 * kWaves)
     const int fi = net.w[l], fo = net.w[l + 1];
     const int i0 = blk / ntn, j0 = blk % ntn * 2;  // blocks of 16
     const int kb = sl * kslice, ke = min(n, kb + kslice);
-    const bf16 *A = net.aT[l] + (size_t)i0 * net.steps * kFrag + 8 * lane;
-    const bf16 *B0 = net.dT[l] + (size_t)j0 * net.steps * kFrag + 8 * lane;
-    const bf16 *B1 = B0 + (size_t)net.steps * kFrag;
+    // an odd last block of d_l stands in for the one past it
+    const int c = lane & 15, quarter = lane >> 4, j1 = 16 * (j0 + 1) < fo ? j0 + 1 : j0;
+    const BatchLane A(net.aT[l], i0, fi, net.steps, c, quarter);
+    const BatchLane B0(net.dT[l], j0, fo, net.steps, c, quarter);
+    const BatchLane B1(net.dT[l], j1, fo, net.steps, c, quarter);
     f32x4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
-#pragma unroll 4
-    for (int k = kb / 32; k < (ke + 31) / 32; ++k) {
-        const size_t o = (size_t)k * kFrag;
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(A + o);
-        const bf16x8 b0 = *reinterpret_cast<const bf16x8 *>(B0 + o);
-        const bf16x8 b1 = *reinterpret_cast<const bf16x8 *>(B1 + o);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, acc[1], 0, 0, 0);
-    }
+    auto product = [&](int sa, int s0, int s1) {
+        const bf16 *pa = A.p + (size_t)(kb / 32) * sa, *p0 = B0.p + (size_t)(kb / 32) * s0,
+                   *p1 = B1.p + (size_t)(kb / 32) * s1;
+        auto load = [](const bf16 *p) { return *reinterpret_cast<const bf16x8 *>(p); };
+        auto mac = [&](bf16x8 a, bf16x8 b0, bf16x8 b1) {
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, acc[1], 0, 0, 0);
+        };
+        int k = (ke - kb + 31) / 32;
+        for (; k >= 4; k -= 4, pa += 4 * sa, p0 += 4 * s0, p1 += 4 * s1) {
+            bf16x8 a[4], b0[4], b1[4];  // four steps' loads in flight
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                a[u] = load(pa + u * sa);
+                b0[u] = load(p0 + u * s0);
+                b1[u] = load(p1 + u * s1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) mac(a[u], b0[u], b1[u]);
+        }
+        for (; k > 0; --k, pa += sa, p0 += s0, p1 += s1) mac(load(pa), load(p0), load(p1));
+    };
+    if (A.step == kFrag && B0.step == kFrag && B1.step == kFrag) product(kFrag, kFrag, kFrag);
+    else product(A.step, B0.step, B1.step);
     float *P = part + (size_t)sl * net.np + net.woff[l];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {

@@ -46,8 +46,9 @@ constexpr int kFuseWidth = 256, kFuseLayers = 6;
 
 // One network and its training workspace as the fused kernels see it.  The
 // matrix-core operands lie in memory as the instruction takes them, in
-// fragments of 16 columns by 32 steps of the inner dimension (frag_index), zero
-// in the padding: a wavefront reads a fragment as 1 KB in a row.
+// fragments of 16 columns by 32 steps of the inner dimension: a wavefront reads a
+// fragment as 1 KB in a row.  The weights' (frag_index) are padded with zeros; the
+// batch arrays hold w_l columns (batch_index).
 struct MlpNet {
     int L;                      // layers
     int w[kFuseLayers + 1];     // widths

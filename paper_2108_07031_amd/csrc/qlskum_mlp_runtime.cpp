@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 using namespace ql;
@@ -32,11 +33,11 @@ struct ql_mlp {
     bf16 *d[2] = {nullptr, nullptr};
     float *part = nullptr, *loss = nullptr;
     float *gpart = nullptr;  // split-K partial products of the weight gradients
-    // the fused kernels' view of a network they serve (act then holds the
-    // transposed activations, dT the transposed errors); net.L = 0: layer by
-    // layer with the buffers d and y
+    // the fused kernels' view of a network they serve, whose buffers (gpart and
+    // part among them) lie in one allocation; net.L = 0: layer by layer with the
+    // buffers above
     MlpNet net{};
-    std::vector<bf16 *> dT;
+    char *block = nullptr;
     int64_t t = 0;  // Adam steps taken
     bool has_weights = false;
 };
@@ -150,43 +151,48 @@ int gradient(ql_mlp *m, const float *X, const float *T, int64_t n) {
     return QL_OK;
 }
 
-// Buffers of the fused path; false (and none kept) if they do not fit, as a
-// network close to the device's memory then runs layer by layer in less.
+// Buffers of the fused path, in one allocation (device allocations are most of what
+// creating a network takes); false if it does not fit, as a network close to the
+// device's memory then runs layer by layer in less.
 bool alloc_fused(ql_mlp *m) {
     const int L = nlayers(m);
     const size_t rows = ((size_t)m->max_batch + 31) / 32 * 32;
-    m->dT.assign(L, nullptr);
-    bool ok = malloc_n(&m->gpart, mlp_part_floats(m->np, m->max_batch)) == hipSuccess &&
-              malloc_n(&m->part, (size_t)mlp_loss_parts(m->max_batch)) == hipSuccess;
-    for (int l = 0; ok && l < L; ++l) {
-        const int fi = mlp_pad(m->widths[l]), fo = mlp_pad(m->widths[l + 1]);
-        const size_t nw = (size_t)fi * fo;
-        ok = malloc_n(&m->act[l], rows * fi) == hipSuccess &&
-             malloc_n(&m->dT[l], rows * fo) == hipSuccess &&
-             malloc_n(&m->Wb[l], nw) == hipSuccess && malloc_n(&m->WbT[l], nw) == hipSuccess;
-    }
-    if (!ok) {
+    MlpNet t{};
+    float *gpart = nullptr, *part = nullptr;
+    size_t size = 0;
+    auto take = [&](auto *&p, size_t count) {
+        p = reinterpret_cast<std::remove_reference_t<decltype(p)>>((uintptr_t)m->block + size);
+        size += (count * sizeof(*p) + 255) / 256 * 256;
+    };
+    auto place = [&] {
+        size = 0;
+        take(gpart, mlp_part_floats(m->np, m->max_batch));
+        take(part, (size_t)mlp_loss_parts(m->max_batch));
+        for (int l = 0; l < L; ++l) {
+            const size_t nw = (size_t)mlp_pad(m->widths[l]) * mlp_pad(m->widths[l + 1]);
+            take(t.aT[l], rows * m->widths[l]);
+            take(t.dT[l], rows * m->widths[l + 1]);
+            take(t.Wf[l], nw);
+            take(t.Wr[l], nw);
+        }
+    };
+    place();  // the size
+    if (malloc_n(&m->block, size) != hipSuccess) {
         (void)hipGetLastError();
-        for (auto *v : {&m->act, &m->dT, &m->Wb, &m->WbT})
-            for (auto &p : *v) free_p(p);
-        free_p(m->gpart);
-        free_p(m->part);
+        m->block = nullptr;
         return false;
     }
-    MlpNet &t = m->net;
-    t.L = L;
+    place();
+    m->gpart = gpart;
+    m->part = part;
     for (int l = 0; l <= L; ++l) t.w[l] = m->widths[l];
-    for (int l = 0; l < L; ++l) {
-        t.woff[l] = m->woff[l];
-        t.Wf[l] = m->WbT[l];
-        t.Wr[l] = m->Wb[l];
-        t.aT[l] = m->act[l];
-        t.dT[l] = m->dT[l];
-    }
+    for (int l = 0; l < L; ++l) t.woff[l] = m->woff[l];
+    t.L = L;
     t.np = m->np;
     t.steps = (int)(rows / 32);
     t.wt = m->w;
     t.g = m->g;
+    m->net = t;
     return true;
 }
 
@@ -287,9 +293,12 @@ int ql_mlp_destroy(ql_mlp *m) {
     for (auto &p : m->Wb) free_p(p);
     for (auto &p : m->WbT) free_p(p);
     for (auto &p : m->act) free_p(p);
-    for (auto &p : m->dT) free_p(p);
-    free_p(m->y); free_p(m->d[0]); free_p(m->d[1]); free_p(m->part); free_p(m->loss);
-    free_p(m->gpart);
+    free_p(m->y); free_p(m->d[0]); free_p(m->d[1]); free_p(m->loss);
+    if (m->block) {
+        m->part = m->gpart = nullptr;  // inside it
+        free_p(m->block);
+    }
+    free_p(m->part); free_p(m->gpart);
     if (m->own_stream && m->stream) (void)hipStreamDestroy(m->stream);
     delete m;
     return QL_OK;
@@ -344,8 +353,8 @@ int ql_mlp_forward(ql_mlp *m, const float *X, float *Y, int64_t n) {
     for (int64_t r = 0; r < n; r += m->max_batch) {
         const int64_t b = std::min(m->max_batch, n - r);
         if (fused) {
-            MCHK(m, launch_to_bf16(m->stream, b, w0, w0, X + r * w0, m->act[0]));
-            MCHK(m, launch_mlp_forward_bf16(m->stream, m->net, m->act[0], Y + r * wL, b));
+            MCHK(m, launch_to_bf16(m->stream, b, w0, w0, X + r * w0, m->net.aT[0]));
+            MCHK(m, launch_mlp_forward_bf16(m->stream, m->net, m->net.aT[0], Y + r * wL, b));
             continue;
         }
         if ((st = forward(m, X + r * w0, b))) return st;
