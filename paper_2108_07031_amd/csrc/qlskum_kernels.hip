@@ -1348,30 +1348,6 @@ __device__ __forceinline__ bool q_to_prim(const double qt[4], const FlowParams &
     return (qt[3] < 0.0) && isfinite(s.p);
 }
 
-// erfc(y)/2 past |y| = kErfNear64, given gauss = exp(-y^2).  Few waves of a
-// transonic flow hold such a state (local Mach above ~1.5), so the
-// coefficients are read from memory in a loop instead of held in registers.
-struct ErfcTable {
-    double c[kErfcN64];
-};
-constexpr ErfcTable erfc_table() {
-    ErfcTable t{};
-    for (int k = 0; k < kErfcN64; ++k) t.c[k] = kErfcPoly64[k];
-    return t;
-}
-__constant__ ErfcTable kErfcTable = erfc_table();
-
-__device__ __forceinline__ double half_erfc_far(double y, double gauss) {
-#pragma clang fp contract(off)
-    const double t = kErfcC64 * fast_rcp(kErfcC64 + fabs(y));
-    const double u = fma(2.0, t, -1.0);
-    double r = kErfcTable.c[kErfcN64 - 1];
-#pragma unroll 1
-    for (int k = kErfcN64 - 2; k >= 0; --k) r = fma(r, u, kErfcTable.c[k]);
-    const double h = (0.5 * gauss) * (t * r);
-    return (y >= 0.0) ? h : 1.0 - h;
-}
-
 // Normal component u_e, S = u_e sqrt(beta), E = exp(-S^2) and A = erfc(-sg S)/2
 // of one split flux.  near() is straight-line code, exact for |S| up to
 // kErfNear64, so that the chains of several fluxes interleave; far() then
@@ -1388,7 +1364,8 @@ struct HalfRange {
         A = half_erfc_near(sg * S);
     }
     __device__ __forceinline__ void far(double sg) {
-        if (fabs(S) > kErfNear64) A = half_erfc_far(-sg * S, E);
+        const double y = -sg * S;
+        if (fabs(S) > kErfNear64) A = half_erfc(y, E, fast_rcp(kErfcC64 + fabs(y)));
     }
 };
 
