@@ -94,8 +94,8 @@ struct Shadow {
 };
 
 // Residual work done by the first nblk workgroups (a multiple of the XCD count)
-// of a first q-derivative pass or an FP64 first-order flux sweep.  step: 2 chunk sums, 3 norms, 4 row counter;
-// nblk 0: none.
+// of a first q-derivative pass or an FP64 first-order flux sweep.  step: 2 chunk
+// sums, 3 norms, 4 row counter; nblk 0: none.
 struct ResRide {
     int nblk = 0, step = 0, n = 0, nchunk = 0, ncase = 0, cap = 0;
     const double *R = nullptr;

@@ -185,15 +185,6 @@ __device__ __forceinline__ double quad_swap(double v) {
     return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// Sum over the kFluxLanes lanes that serve one point, in the fixed order
-// (l0 + l1) + (l2 + l3); every lane of the group receives the same value
-// (floating-point addition is commutative).
-__device__ __forceinline__ double lane_group_sum(double v) {
-    v += quad_swap<kQuadXor1>(v);
-    v += quad_swap<kQuadXor2>(v);
-    return v;
-}
-
 // Lane l's copy of v, on every lane of the quad.
 template <int L>
 __device__ __forceinline__ double quad_bcast(double v) {
@@ -206,8 +197,9 @@ __device__ __forceinline__ double pick4(const double v[4], int sub) {
     return (sub & 2) ? b : a;
 }
 
-// lane_group_sum of v[sub] on lane sub, with the same order of additions: each
-// exchange sends the half of the components that the partner keeps.
+// Sum of v[sub] over the kFluxLanes lanes that serve one point, on lane sub, in the
+// fixed order (l0 + l1) + (l2 + l3): each exchange sends the half of the components
+// that the partner keeps (floating-point addition is commutative).
 __device__ __forceinline__ double lane_group_sum4(const double v[4], int sub) {
     const bool odd = (sub & 1) != 0, high = (sub & 2) != 0;
     const double a = (odd ? v[1] : v[0]) + quad_swap<kQuadXor1>(odd ? v[0] : v[1]);
@@ -570,7 +562,7 @@ hipError_t launch_prep(hipStream_t st, const DevCloud &c, const FlowParams &fp, 
 // workgroup owns kFluxTile consecutive points, stages the records its
 // entries gather (its own points and its halo) in LDS, and serves each point
 // with kFluxLanes lanes that walk every kFluxLanes-th entry; the lane sums
-// are combined in a fixed order (lane_group_sum), so each point's sums have
+// are combined in a fixed order (lane_group_sum4's), so each point's sums have
 // one order whichever path (LDS or memory) a tile takes.  The full-stencil
 // least-squares matrix is inverted once at set-up (lsi = (Syy, Sxy, Sxx)/Det).
 // ---------------------------------------------------------------------------
@@ -612,7 +604,7 @@ __device__ __forceinline__ float vmax_neg(float a, float b) {
 // These ends of the sweeps were most of their instructions (first pass: 500 of
 // 623 per wave) while every lane reduced and selected all eight values.
 
-// Components 2 (sub & 1), 2 (sub & 1) + 1 of lane_group_sum, in its order.
+// Components 2 (sub & 1), 2 (sub & 1) + 1 of the lanes' sum, in lane_group_sum4's order.
 __device__ __forceinline__ void lane_group_sum_pair(const double v[4], int sub, double out[2]) {
     const bool odd = (sub & 1) != 0;
 #pragma unroll
@@ -1185,10 +1177,10 @@ static int lds_cap(const DevCloud &c, int budget, int rec) {
 // caller gives no budget (records of 48 and 80 bytes; 4 KB of entry slots
 // come on top: reading the first pass's slots from memory instead, one dependent
 // load per entry, took 206 us on the 2.5M cloud against 160, on FP32 data 161
-// against 131).  Sized so that the 6 workgroups per CU
-// that the kernels' registers allow stay resident in 160 KB of LDS
-// (measured on the 2.5M cloud: 22 KB runs the inner iteration 12% faster
-// than 36 KB, although a few more tiles then read from memory).
+// against 131).  Sized so that 6 workgroups per CU stay resident in 160 KB of LDS:
+// the first pass's registers allow as many (80), the inner iteration's 7 (72)
+// (measured on the 2.5M cloud with an earlier form of the kernel: 22 KB runs the inner
+// iteration 12% faster than 36 KB, although a few more tiles then read from memory).
 constexpr int kGrad0Lds = 26 * 1024 - 2 * kCapE;
 constexpr int kGradkLds = 22 * 1024;
 // The FP32-data inner iteration fits 64 VGPRs, i.e. 8 waves per SIMD: 8
@@ -1682,14 +1674,14 @@ __device__ __forceinline__ void finish_point(const DevCloud &cl, const FlowParam
 // A workgroup owns a tile of kFluxTile consecutive points (a compact patch in
 // Hilbert order) and serves each point with kFluxLanes lanes: lane l walks the
 // point's neighbour entries l, l + kFluxLanes, ... and the partial sums are
-// combined by lane_group_sum, so every point's residual is summed in one fixed
+// combined by lane_group_sum4, so every point's residual is summed in one fixed
 // order.  The records that the entries gather (q, q-derivatives, limiter
 // bounds, position) of the tile's points and of its halo are first copied
 // into LDS; each is read from memory once per tile instead of once per use.
 // A tile whose image exceeds the capacity `cap` (slots) reads straight from
 // memory (a branch uniform across the workgroup), with the same arithmetic.
 //
-// stage 0: evaluate R only (into Rout).  stage 1..4: residual + rk_update;
+// stage 0: evaluate R only (into Rout).  stage 1..4: residual + quad_update;
 // stage 1 also writes R to Rout for the residual norm.  Frozen points, and
 // outer points unless KOBC, are held (q copied to qnext) and carry R = 0.
 // Kinetic outer condition (fp.kobc): outer points take their s+, s-, n+
@@ -2072,7 +2064,6 @@ k_flux_first(DevCloud cl, FlowParams fp, int stage, int cap, const double2 *__re
     }
     const int t = sweep_tile(cl, ride.nblk);
     if (cl.tile_active && !cl.tile_active[t]) return;
-    if (cl.tile_prec && cl.tile_prec[t] != 0) return;  // an FP32-flux tile
     const TileInfo ti = tile_info(cl, t, cap);
     const int j = threadIdx.x / kFluxLanes, sub = threadIdx.x % kFluxLanes;
     const int p = ti.base + j;

@@ -609,27 +609,32 @@ int prep_state(ql_solver *s) {
 
 // LDS bytes a flux workgroup may stage its tile image in.  The defaults keep
 // the workgroups that the kernels' register use allows per CU resident
-// (3 for FP64 with the limiter, 4 otherwise; 160 KB of LDS per CU).
+// (3 for FP64 with the limiter, 4 otherwise; 160 KB of LDS per CU).  The FP64
+// first-order sweep takes the same two, though it does not use the limiter and holds
+// 8 KB besides: less (32 KB, with which four workgroups fit whatever the largest
+// image) gains nothing where one image is large (400k points, one of 777 records:
+// 187 us at 40 KB, 189 at 32, 190 at 52) and loses where many are (100k points of 140
+// neighbours, half the images past 409 records: 92 us at 40 KB, 91 at 52, 109 at 32).
 int flux_lds_budget(const ql_solver *s) {
     if (s->prm.flux_lds > 0) return s->prm.flux_lds;
     return (s->prm.precision == 0 && s->prm.limiter) ? 52 * 1024 : 40 * 1024;
 }
 
-// One flux-residual launch (stage 0: evaluate into R; 1..4: RK stage).
+// One flux-residual launch (stage 0: evaluate into R; 1..4: RK stage); ride: FP64
+// first order only.
 int launch_stage(ql_solver *s, const DevCloud &c, const FlowParams &fp, int stage, double *Rout,
                  const ResRide &ride = {}) {
     const int a = s->qcur, b = 1 - s->qcur;
     const int lds = flux_lds_budget(s);
     if (s->hybrid) {
-        // each kernel takes the tiles of its precision (tile_prec); the FP64
-        // one with its own default LDS budget
+        // second order: each kernel takes the tiles of its precision (tile_prec); the
+        // FP64 one with its own default LDS budget
         ql_params saved = s->prm;
         s->prm.precision = 0;
         const int lds64 = flux_lds_budget(s);
         s->prm = saved;
         HIPCHK(s, launch_flux(s->stream, c, fp, stage, lds64, s->q[a], s->g[s->gfin], s->qmm, s->U,
-                              s->Un, s->dt, s->q[b], Rout, s->q32[b], s->errw, 0, s->Rpart,
-                              ride));
+                              s->Un, s->dt, s->q[b], Rout, s->q32[b], s->errw, 0, s->Rpart));
         HIPCHK(s, launch_flux_mixed(s->stream, c, fp, stage, lds, s->q[a], s->q32[a], s->g32,
                                     s->qmm32, s->U, s->Un, s->dt, s->q[b], s->q32[b], Rout,
                                     s->errw));
@@ -654,7 +659,7 @@ int launch_stage(ql_solver *s, const DevCloud &c, const FlowParams &fp, int stag
 // launches of their own.
 int enqueue_iteration(ql_solver *s, const DevCloud &c, const FlowParams &fp, int hist_cap,
                       double *hist) {
-    const bool ride = (fp.order == 2 || s->prm.precision == 0 || s->hybrid) &&
+    const bool ride = (fp.order == 2 || s->prm.precision == 0) &&
                       (!s->timing || s->capturing || s->no_alloc);
     const double *inv_nupd = s->inv_nupd + (fp.kobc ? s->ncase : 0);
     for (int rk = 1; rk <= 4; ++rk) {
