@@ -232,12 +232,8 @@ int check_batch(ql_mlp *m, const void *X, const void *T, int64_t n, bool need_t)
     return QL_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-int ql_mlp_create(ql_mlp **out, int32_t device, void *hip_stream, const int32_t *widths,
-                  int32_t nwidth, int64_t max_batch) {
+int create(ql_mlp **out, int32_t device, void *hip_stream, const int32_t *widths, int32_t nwidth,
+           int64_t max_batch, bool fuse) {
     if (!out) return QL_EINVAL;
     *out = nullptr;
     if (!widths || nwidth < 2 || max_batch < 1 || max_batch > (int64_t)1 << 26) return QL_EINVAL;
@@ -275,7 +271,7 @@ int ql_mlp_create(ql_mlp **out, int32_t device, void *hip_stream, const int32_t 
     m->WbT.assign(nwidth - 1, nullptr);
     m->act.assign(nwidth - 1, nullptr);
     okm = okm && malloc_n(&m->loss, 1) == hipSuccess;
-    if (okm && !(mlp_fusable(m->widths.data(), nwidth) && alloc_fused(m)))
+    if (okm && !(fuse && mlp_fusable(m->widths.data(), nwidth) && alloc_fused(m)))
         okm = alloc_layers(m, maxw);
     if (!okm) {
         ql_mlp_destroy(m);
@@ -283,6 +279,22 @@ int ql_mlp_create(ql_mlp **out, int32_t device, void *hip_stream, const int32_t 
     }
     *out = m;
     return QL_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int ql_mlp_create(ql_mlp **out, int32_t device, void *hip_stream, const int32_t *widths,
+                  int32_t nwidth, int64_t max_batch) {
+    return create(out, device, hip_stream, widths, nwidth, max_batch, true);
+}
+
+// A network that runs layer by layer whatever its widths, as one whose fused buffers
+// do not fit does.  Not in the public header: tests hold the two paths to the same bits.
+int ql_mlp_create_layered(ql_mlp **out, int32_t device, void *hip_stream, const int32_t *widths,
+                          int32_t nwidth, int64_t max_batch) {
+    return create(out, device, hip_stream, widths, nwidth, max_batch, false);
 }
 
 int ql_mlp_destroy(ql_mlp *m) {
