@@ -1355,9 +1355,16 @@ struct HalfRange {
         E = gauss(S);
         A = half_erfc_near(sg * S);
     }
+    // RARE keeps the compiler from forming the reciprocal ahead of the branch (flux
+    // without the limiter, 632k points: 223 -> 220 us; with the limiter the same hint
+    // spills eight registers more, 279 -> 282)
+    template <bool RARE = false>
     __device__ __forceinline__ void far(double sg) {
-        const double y = -sg * S;
-        if (fabs(S) > kErfNear64) A = half_erfc(y, E, fast_rcp(kErfcC64 + fabs(y)));
+        const bool past = fabs(S) > kErfNear64;
+        if (RARE ? __builtin_expect(past, 0) : past) {
+            const double y = -sg * S;
+            A = half_erfc(y, E, fast_rcp(kErfcC64 + fabs(y)));
+        }
     }
 };
 
@@ -1503,12 +1510,12 @@ __device__ __forceinline__ bool flux_entry(uint8_t f, double dx, double dy, doub
     }
     if (far > kErfNear64) {
         if (kS) {
-            hs[0].far(sgs);
-            hs[1].far(sgs);
+            hs[0].far<!LIMITER>(sgs);
+            hs[1].far<!LIMITER>(sgs);
         }
         if (kN) {
-            hn[0].far(sgn);
-            hn[1].far(sgn);
+            hn[0].far<!LIMITER>(sgn);
+            hn[1].far<!LIMITER>(sgn);
         }
     }
     double Gi[4], G0[4];
