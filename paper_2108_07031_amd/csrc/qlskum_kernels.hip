@@ -1856,16 +1856,37 @@ __device__ __forceinline__ bool flux_point(const DevCloud &cl, const FlowParams 
     return ok;
 }
 
+// The arrays of the kernel's DevCloud, its first argument, read again from the
+// argument segment through an address that the compiler cannot relate to it: values
+// it keeps in no register meanwhile.
+__device__ __forceinline__ DevCloud reload_cloud() {
+    unsigned long long at = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    const auto *a = (const __attribute__((address_space(4))) DevCloud *)at;
+    DevCloud c{};
+    c.xy = a->xy;
+    c.nrm = a->nrm;
+    c.kind = a->kind;
+    c.ptr = a->ptr;
+    c.idx = a->idx;
+    c.flag = a->flag;
+    c.lsw = a->lsw;
+    c.case_of = a->case_of;
+    c.uinf = a->uinf;
+    return c;
+}
+
 // The sums of a point of k_flux that failed, from memory and with one reciprocal
-// per limiter value.  Everything is read again through an index that the compiler
-// cannot relate to p, so that the sweep holds no register for this rare path (kept in
-// registers, it slowed the launch by 3%; read again, by 1%: 1054 -> 1065 us at 2.5M
-// points.  A reciprocal per limiter value in the sweep itself would take 16 more of
-// its 494 instructions per entry).
+// per limiter value.  Everything is read again, the point through an index that the
+// compiler cannot relate to p, so that the sweep holds no register for this rare path:
+// the launch takes its time without it (632k points 272 us; with the point's data held
+// 281, with the arrays' addresses held 278.  A reciprocal per limiter value in the
+// sweep itself would take 16 more of its ~500 instructions per entry).
 template <int POW, int M, bool KOBC>
-__device__ __forceinline__ bool flux_point_wide(const DevCloud &cl, const FlowParams &fp, int p,
-                                                int sub, const double2 *q, const double2 *g,
+__device__ __forceinline__ bool flux_point_wide(const FlowParams &fp, int p, int sub,
+                                                const double2 *q, const double2 *g,
                                                 const double2 *qmm, double R[4]) {
+    const DevCloud cl = reload_cloud();
     asm volatile("" : "+v"(p));
     OwnPoint o;
     o.load(cl, p, sub);
@@ -1876,6 +1897,7 @@ __device__ __forceinline__ bool flux_point_wide(const DevCloud &cl, const FlowPa
 
 }  // namespace
 
+// cl has to stay the first argument (reload_cloud).
 template <bool LIMITER, int POW, int M, bool KOBC>
 // Held to 3 waves per SIMD (at most 168 VGPRs), which the straight-line
 // two-direction body of flux_entry would otherwise exceed.  Bound by FP64 issue
@@ -1932,7 +1954,7 @@ k_flux(DevCloud cl, FlowParams fp, int stage, int cap,
         bool ok = in_lds ? flux_point<true, LIMITER, POW, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R)
                          : flux_point<false, LIMITER, POW, M, KOBC>(cl, fp, lds, j, p, o, q, g, qmm, R);
         if constexpr (LIMITER) {
-            if (!ok) ok = flux_point_wide<POW, M, KOBC>(cl, fp, p, sub, q, g, qmm, R);
+            if (!ok) ok = flux_point_wide<POW, M, KOBC>(fp, p, sub, q, g, qmm, R);
         }
         if (!ok) report_pt(cl, err, p, kErrPositivity);
     }
