@@ -1439,8 +1439,8 @@ __device__ __forceinline__ void venkat2(double da, const double *ba, double db, 
 }
 
 // Contribution of one neighbour entry (split flags f, offset (dx, dy) from p
-// to i) to the residual of p.  Bound by FP64 issue: 494 VALU instructions with
-// the limiter, seven of them quarter-rate (a reciprocal per limiter value and
+// to i) to the residual of p.  Bound by FP64 issue: about 490 VALU instructions
+// with the limiter, seven of them quarter-rate (a reciprocal per limiter value and
 // the general erfc everywhere took 630 with seventeen); by itself that took the
 // 2.5M-point launch from 1595 to 1352 us.  Forms the modified states q~_i and q~_p of eq. (28)
 // (limited when LIMITER), their split fluxes, and w_b (G(q~_i) - G(q~_p))
@@ -1881,7 +1881,7 @@ __device__ __forceinline__ DevCloud reload_cloud() {
 // compiler cannot relate to p, so that the sweep holds no register for this rare path:
 // the launch takes its time without it (632k points 272 us; with the point's data held
 // 281, with the arrays' addresses held 278.  A reciprocal per limiter value in the
-// sweep itself would take 16 more of its ~500 instructions per entry).
+// sweep itself would take 16 more instructions per entry).
 template <int POW, int M, bool KOBC>
 __device__ __forceinline__ bool flux_point_wide(const FlowParams &fp, int p, int sub,
                                                 const double2 *q, const double2 *g,
@@ -1901,7 +1901,7 @@ __device__ __forceinline__ bool flux_point_wide(const FlowParams &fp, int p, int
 template <bool LIMITER, int POW, int M, bool KOBC>
 // Held to 3 waves per SIMD (at most 168 VGPRs), which the straight-line
 // two-direction body of flux_entry would otherwise exceed.  Bound by FP64 issue
-// (82% of the SIMD cycles): on the 2.5M cloud with the limiter 1568 -> 1058 us
+// (86% of the SIMD cycles): on the 2.5M cloud with the limiter 1568 -> 1054 us
 // (flux_entry, stage_records with OwnPoint's loads, quad_update).  Slower, with
 // the same bits: the least-squares factors in LDS instead of registers (632k
 // points 272 -> 281 us), the tile's points finished by one wavefront (346).
