@@ -46,7 +46,10 @@ FLOPS_PER_ENTRY_UNIT = {1: 940, 0: 690}
 # An itemised count of the same launch, reported beside it: per neighbour
 # entry that enters at least one split stencil, and per split stencil it
 # enters; transcendentals and divides at fixed costs (exp 20, log 20,
-# erfc 30, sqrt 10, divide 10).
+# erfc 30, sqrt 10, divide 10).  A nominal unit like the other: it prices the
+# formulas, not the kernel's shorter forms of them (paired limiter
+# reciprocals, erf's polynomial near 0); what the kernel executes is the
+# hardware count in profiles/pmc_valu_flux_c2_fp64.md.
 FLOPS_ENTRY_COMMON = 202       # geometry, reconstruction, two q~ -> primitive states
 FLOPS_ENTRY_LIMITER = 125      # Venkatakrishnan factors of 8 increments, eps^2
 FLOPS_PER_STENCIL = 191        # two split fluxes, their difference, weighted sum

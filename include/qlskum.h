@@ -309,8 +309,9 @@ int ql_batch_forces(ql_solver *s, double *cl, double *cd);
  * fields gives a start closer to the solution (the paper's method starts
  * from the freestream; this is an addition to it).  The network object is
  * separate from the solver; max_batch
- * bounds the rows of one training step (inference is chunked).  The
- * library owns all device buffers; hip_stream as in ql_create.
+ * bounds the rows of one training step (inference takes any number).  The
+ * library owns all device buffers, sized for training at creation;
+ * hip_stream as in ql_create.
  * Weights are one FP32 vector: for each layer l, W_l row-major
  * (widths[l] x widths[l+1]) then b_l (widths[l+1]).
  * Errors: QL_EINVAL (widths outside 1..4096, fewer than 2, max_batch
@@ -383,7 +384,8 @@ int ql_evaluate(ql_solver *s);
  * tile's LDS image holds (its points plus its halo).  A tile is staged in
  * LDS when slots * record bytes <= the flux_lds budget; the record is 176
  * bytes (FP64 with limiter), 112 (FP64), 96 (mixed with limiter) or 64
- * (mixed).  Errors: QL_EINVAL (NULL), QL_ESTATE (no cloud). */
+ * (mixed); first order 80 (FP64; at most 152 KB of images, as the kernel holds
+ * 8 KB besides) or 32 (mixed).  Errors: QL_EINVAL (NULL), QL_ESTATE (no cloud). */
 int ql_flux_tiles(const ql_solver *s, int32_t *ntile, int32_t *slots);
 
 /* Autotuning of the tiled sweeps: times the flux sweep (stage evaluation)
@@ -422,7 +424,9 @@ int ql_cloud_size(const ql_solver *s, int64_t *n, int64_t *nnz);
  * events on the solver's stream.  ql_kernel_time returns, for kernel kind
  * `which` (0 gradient first pass, 1 gradient inner iteration, 2 flux
  * residual + update, 3 residual norm), the summed duration in ms and the
- * launch count since timing was last enabled.  Errors: QL_EINVAL. */
+ * launch count since timing was last enabled.  A timed run forms the residual
+ * norms in launches of their own, where others form them inside the sweeps
+ * (the same bits).  Errors: QL_EINVAL. */
 int ql_set_timing(ql_solver *s, int32_t enable);
 int ql_kernel_time(const ql_solver *s, int32_t which, double *total_ms, int64_t *count);
 
